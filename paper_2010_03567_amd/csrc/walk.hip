@@ -245,6 +245,14 @@ __device__ __forceinline__ void eval_high(const float *o, const double *u4, floa
 #define WK_SPILL G4_WALK_SPILL
 #define WK_RING 128  // ring capacity: < 64 pending before an append of <= 64
 
+// Idle lanes of the pair phase wait until this many of them can end their items
+// and take the next ones together.  The items of a step end one by one (leaves
+// of 1 to leaf_max particles), so at 1 nearly every step paid for the sums and
+// the refill of a few lanes; at 32 the waiting lanes cost more than that.
+// 2^24 particles, relative walk: 45.3 ms at 1, 44.64 at 8, 44.55 at 12, 44.58
+// at 16, 45.0 at 24, 45.7 at 32 (2^21: 4.65 / 4.58 / 4.56 / 4.59 / 4.63 / 4.70).
+#define WK_REFILL 12
+
 #define NUM_LEAF (1u << 31)  // leaf bit of VisitRec::numleaf
 // Entries with fewer (child, target) slots than this skip the decisions for the
 // whole group (their cost per entry outweighs the visit passes they save).
@@ -529,10 +537,10 @@ __global__ __launch_bounds__(256, WALK_MIN_WAVES(KER, POT, HI)) void k_walk(cons
     float q_fx = 0.f, q_fy = 0.f, q_fz = 0.f, q_fp = 0.f;
     wave_sync_lds();
 
-    // Particle pairs from the leaf ring: idle lanes take the next items in ring
-    // order; every step evaluates one pair per busy lane.  Without `drain` the
-    // phase ends as soon as a lane cannot be refilled, so every step is full;
-    // lanes keep their unfinished items for the next phase.
+    // Particle pairs from the leaf ring: every step evaluates one pair per busy
+    // lane; once WK_REFILL lanes are idle they add their sums and take the next
+    // items in ring order.  Without `drain` the phase ends when they cannot be
+    // refilled; lanes keep their unfinished items (and sums) for the next phase.
     // One pair for every lane that holds an item.  The target itself is among
     // the sources of its own leaf: its separation is zero, where the kernel
     // is finite, so its force term is exactly zero and only the potential
@@ -563,6 +571,10 @@ __global__ __launch_bounds__(256, WALK_MIN_WAVES(KER, POT, HI)) void k_walk(cons
         }
         q_src++;
         q_rem--;
+    };
+    // the sums of the items that ended go to their targets (a lane that never
+    // had an item adds zero to target 0)
+    auto flush_items = [&]() {
         if (q_rem == 0) {
             lds_add(&W.acc[0][q_t], (double)q_fx);
             lds_add(&W.acc[1][q_t], (double)q_fy);
@@ -574,42 +586,40 @@ __global__ __launch_bounds__(256, WALK_MIN_WAVES(KER, POT, HI)) void k_walk(cons
     auto run_pairs = [&](bool drain) {
         w_phase++;
         for (;;) {
-            const uint64_t idle = ballot(q_rem == 0);
-            const uint32_t avail = lt_t - lt_h;
-            if (idle && avail) {
-                const uint32_t r = lanes_below(idle);
-                if (q_rem == 0 && r < avail) {
-                    const uint32_t q = (lt_h + r) & (WK_RING - 1);
-                    q_src = W.lt_first[q];
-                    q_rem = W.lt_num[q];
-                    q_t = W.lt_tgt[q];
-                    const uint4 T = W.tgt[q_t];
-                    q_x = T.x;
-                    q_y = T.y;
-                    q_z = T.z;
-                    q_self = (uint32_t)i0 + q_t;  // sorted index of the target itself
-                    if (A.stat) {
-                        // the pair count only when it is read; the empty statement keeps the
-                        // count behind the branch instead of a select after it
-                        uint32_t nq = q_rem;
-                        asm volatile("" : "+v"(nq));
-                        t_pp += nq - ((q_self - q_src) < nq ? 1u : 0u);
-                    }
-                }
-                lt_h += min((uint32_t)__builtin_popcountll(idle), avail);
-            }
             const uint64_t busy = ballot(q_rem != 0);
-            if (drain) {
-                if (!busy) break;
-                w_pp++;
-                if (q_rem != 0) pair_step();
-            } else {
-                // every lane holds an item (busy is all ones)
-                if (busy != ~0ull) break;
-                w_pp++;
-                pair_step();
+            if ((uint32_t)__builtin_popcountll(busy) <= 64u - WK_REFILL) {
+                const uint32_t avail = lt_t - lt_h;
+                if (avail) {
+                    const uint64_t idle = ~busy;
+                    const uint32_t r = lanes_below(idle);
+                    flush_items();
+                    if (q_rem == 0 && r < avail) {
+                        const uint32_t q = (lt_h + r) & (WK_RING - 1);
+                        q_src = W.lt_first[q];
+                        q_rem = W.lt_num[q];
+                        q_t = W.lt_tgt[q];
+                        const uint4 T = W.tgt[q_t];
+                        q_x = T.x;
+                        q_y = T.y;
+                        q_z = T.z;
+                        q_self = (uint32_t)i0 + q_t;  // sorted index of the target itself
+                        if (A.stat) {
+                            // the pair count only when it is read; the empty statement keeps the
+                            // count behind the branch instead of a select after it
+                            uint32_t nq = q_rem;
+                            asm volatile("" : "+v"(nq));
+                            t_pp += nq - ((q_self - q_src) < nq ? 1u : 0u);
+                        }
+                    }
+                    lt_h += min((uint32_t)__builtin_popcountll(idle), avail);
+                } else if (!drain || !busy) {
+                    break;
+                }
             }
+            w_pp++;
+            if (q_rem != 0) pair_step();
         }
+        if (drain) flush_items();
     };
 
     while (sp > 0) {
