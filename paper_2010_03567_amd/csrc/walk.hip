@@ -15,6 +15,7 @@
 // the kernel below).  Interactions are FP32 arithmetic on int32 nearest-image
 // differences, summed per target in FP64.
 #include <algorithm>
+#include <cmath>
 #include <cstdlib>
 #include <new>
 #include <vector>
@@ -934,6 +935,24 @@ __global__ void k_srtab(float4 *__restrict__ tab, int n)
                            (float)(2.0 * (f0 - f1) + d0 + d1));
 }
 
+// Targets per wavefront: the caller's group size (64 if it gives none), but no
+// more than sqrt(n)/22, at least 2.  A group is walked by one wavefront from
+// the root to the leaves, a serial chain of some hundred tree entries, so with
+// few particles groups of 64 leave most of the 1024 SIMDs without work (8192
+// particles: 128 wavefronts), while with many particles small groups repeat
+// the traversal too often.  The best sizes found for n = 1500, 8192, 30 k,
+// 100 k, 300 k, 10^6, 2^21 are 2-4, 8, 8, 8-16, 24, 32-48, 64 (Newtonian and
+// TreePM; Ewald 110 k: 8-16), which grow like the square root.  Relative walk
+// at 64 and at the rule's size: 8192 Newtonian 0.76 and 0.30 ms, 50 k TreePM
+// 0.85 and 0.34, 110 k Ewald 4.77 and 2.85, 500 k TreePM 1.85 and 1.68.
+// Decisions are taken per target, so results do not depend on the size (the
+// FP64 sums only in their order).
+static int walk_group(int asked, int64_t n)
+{
+    const int limit = (int)std::min(64.0, std::max(2.0, std::sqrt((double)n) / 22.0));
+    return std::min(asked > 0 && asked <= 64 ? asked : 64, limit);
+}
+
 int g4_launch_walk(g4_ctx *ctx, g4_tree *t, const g4_walk_params *wp, int kernel, int criterion, double *ax,
                    double *ay, double *az, double *pot, uint32_t *counts, float *aout_caller, float *aout_sorted,
                    int stat_slot, bool count)
@@ -945,7 +964,7 @@ int g4_launch_walk(g4_ctx *ctx, g4_tree *t, const g4_walk_params *wp, int kernel
     A.aseed = t->aseed;
     A.perm = t->perm1;
     A.n = t->n;
-    A.group = wp->group_size > 0 && wp->group_size <= 64 ? wp->group_size : 64;
+    A.group = walk_group(wp->group_size, t->n);
     A.S = t->S;
     A.exclusion = wp->exclusion ? 1 : 0;
     A.order = wp->order;
