@@ -10,39 +10,48 @@
 // axis) once for each.  The potential carries the sign of the Newtonian one
 // (attractive): phi_lr = -G (4 pi / V) sum_{k != 0} exp(-k^2 r_s^2)/k^2 ...
 //
-// Layout: an ng^3 mesh of complex FP32 (z fastest), mesh point c at c h,
-// h = L / ng.  The particles come from a built tree in curve order (so that
-// neighbouring threads touch neighbouring cells) with 32-bit integer
+// Layout: an ng^3 real FP32 mesh (z fastest), mesh point c at c h, h = L / ng,
+// and its transform along z as ng/2 + 1 complex values per row (the rest is
+// their conjugate).  The particles come from a built tree in curve order (so
+// that neighbouring threads touch neighbouring cells) with 32-bit integer
 // coordinates: for ng = 2^g the cell is the top g bits and the CIC weight
 // the remaining bits, both exact.
 //
-// Steps: k_pm_deposit (8 float atomics per particle) -> three passes of
-// k_pm_fft (ng-point radix-2 transforms of tiles of lines staged in LDS, one
-// pass per axis; the tiles of the strided axes take consecutive lines so
-// every load and store is a run of consecutive cells) -> k_pm_green -> three
-// inverse passes, the last one keeping only the real part -> k_pm_interp
+// Steps: k_pm_deposit (8 float atomics per particle) -> k_pm_z_forward (two
+// real lines as one complex transform) -> k_pm_lines along y -> k_pm_lines
+// along x: forward, Green's function and inverse in one pass -> inverse along
+// y -> k_pm_z_inverse, which leaves the real potential -> k_pm_interp
 // (gradient and interpolation fused: each particle reads the potential around
 // its 8 CIC points).
+#include <algorithm>
 #include <cmath>
 
 #include "g4_internal.h"
 
-#define PM_THREADS 256
-#define PM_TILE_CELLS 4096  // complex cells per FFT tile (32 KiB of LDS, plus the twiddles)
+// Complex values per row of the half spectrum: ng/2 + 1, padded so that rows
+// of the larger meshes start on 64-byte boundaries.
+__host__ __device__ constexpr int pm_pitch(int ng) { return ng / 2 + (ng >= 64 ? 8 : 1); }
 
-__global__ void k_pm_twiddle(float2 *__restrict__ tw, int ng)
+// Tables, in FP64 rounded once: tw[m] = exp(-2 pi i m / ng), m < ng, and per
+// axis gt[i] = exp(-k^2 r_s^2) / sinc^4(pi n / ng), k = 2 pi n / L, n the signed
+// wave number of index i (the Gaussian and the twice deconvolved CIC window of
+// the Green's function factorise over the axes).
+__global__ void k_pm_tables(float2 *__restrict__ tw, float *__restrict__ gt, int ng, double box, double r_s)
 {
-    const int k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= ng / 2) return;
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= ng) return;
     double s, c;
-    sincospi(-2.0 * (double)k / (double)ng, &s, &c);  // exp(-2 pi i k / ng)
-    tw[k] = make_float2((float)c, (float)s);
+    sincospi(-2.0 * (double)i / (double)ng, &s, &c);
+    tw[i] = make_float2((float)c, (float)s);
+    const int n = i < ng / 2 ? i : i - ng;
+    const double k = 2.0 * M_PI * n / box, u = M_PI * n / ng, w = n ? sin(u) / u : 1.0;
+    gt[i] = (float)(exp(-k * k * r_s * r_s) / (w * w * w * w));
 }
 
-__global__ void k_pm_clear(float2 *__restrict__ m, size_t ncell)
+__global__ void k_pm_clear(float4 *__restrict__ m, size_t nvec)
 {
-    for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < ncell; i += (size_t)gridDim.x * blockDim.x)
-        m[i] = make_float2(0.f, 0.f);
+    for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < nvec; i += (size_t)gridDim.x * blockDim.x)
+        m[i] = make_float4(0.f, 0.f, 0.f, 0.f);
 }
 
 // CIC cell and upper weight of one coordinate: top g bits, remaining bits / 2^(32-g)
@@ -58,7 +67,7 @@ __device__ __forceinline__ void pm_cell(uint32_t X, int shift, float wscale, int
 // over such runs by a segmented scan across the wavefront and the last lane
 // of a run issues the one atomic: in haloes most atomics disappear.
 __global__ void k_pm_deposit(const uint4 *__restrict__ parts, int64_t n, int ng, int shift, float wscale,
-                             float2 *__restrict__ mesh)
+                             float *__restrict__ mesh)
 {
     const int lane = threadIdx.x & 63;
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
@@ -86,141 +95,248 @@ __global__ void k_pm_deposit(const uint4 *__restrict__ parts, int64_t n, int ng,
                 if (lane >= off && ku == key) v += vu;
             }
             const uint32_t kd = (uint32_t)__shfl_down((int)key, 1);
-            if (act && (lane == 63 || kd != key)) atomicAdd(&mesh[key].x, v);
+            if (act && (lane == 63 || kd != key)) atomicAdd(&mesh[key], v);
         }
     }
 }
 
-// One pass of ng-point transforms along `axis` (0 x, 1 y, 2 z) over every
-// line of the mesh.  A block takes tl lines: for z, tl consecutive lines
-// (one contiguous run of tl ng cells); for y and x, tl lines that are
-// neighbours in z, so each of the ng rows of the tile is a run of tl cells.
-// In LDS: bit-reversed load, lg in-place radix-2 stages, natural-order store.
-// sign -1: forward (exp(-i k x)); +1: inverse, unnormalised.  real_out, if
-// given, receives the real part instead of the complex result.
-__global__ __launch_bounds__(PM_THREADS) void k_pm_fft(float2 *__restrict__ data, const float2 *__restrict__ tw,
-                                                        int ng, int lg, int tl, int axis, float sign,
-                                                        float *__restrict__ real_out)
+// ---------------------------------------------------------------- transforms
+// An N-point line (N = 8 .. 1024) is held by N / 8 threads, 8 points each in
+// registers: thread j holds points j + q N / 8.  Radix-8 steps (self-sorting
+// order, the last one of radix 2 or 4 where log2 N is no multiple of 3) exchange
+// through LDS in between, so 512 points cross it twice (an in-place transform
+// in LDS with fused radix-2 pairs crossed it ten times).  Global loads and stores
+// go straight between registers and memory.  Every pass is bound by HBM: 8 or
+// 6 bytes per mesh point and pass, 44 for a call where the complex mesh moved
+// 120.  Mesh 512^3, 2^24 particles: transforms and Green's function 6.3 -> 1.0 ms.
+__device__ __forceinline__ float2 c_add(float2 a, float2 b) { return make_float2(a.x + b.x, a.y + b.y); }
+__device__ __forceinline__ float2 c_sub(float2 a, float2 b) { return make_float2(a.x - b.x, a.y - b.y); }
+__device__ __forceinline__ float2 c_mul(float2 a, float2 w) { return make_float2(a.x * w.x - a.y * w.y, a.x * w.y + a.y * w.x); }
+// times exp(SIGN i pi / 2)
+template <int SIGN>
+__device__ __forceinline__ float2 c_quarter(float2 a)
 {
-    extern __shared__ float2 sm[];
-    const int tid = threadIdx.x;
-    const int cells = tl * ng;
-    float2 *tws = sm + cells;  // twiddles of this direction: exp(sign 2 pi i k / ng), k < ng/2
-    for (int k = tid; k < ng / 2; k += PM_THREADS) {
-        const float2 w = tw[k];
-        tws[k] = make_float2(w.x, -sign * w.y);
-    }
-    size_t base;
-    size_t estride;  // distance between consecutive points of one line
-    size_t lstride;  // distance between the tile's lines
-    if (axis == 2) {
-        base = (size_t)blockIdx.x * cells;
-        estride = 1;
-        lstride = ng;
-    } else {
-        const int per = ng / tl;  // tiles per outer index
-        const size_t outer = blockIdx.x / per, z0 = (size_t)(blockIdx.x % per) * tl;
-        estride = axis == 1 ? (size_t)ng : (size_t)ng * ng;
-        base = (axis == 1 ? outer * ng * ng : outer * ng) + z0;
-        lstride = 1;
-    }
-    // load: consecutive threads take consecutive addresses
-    for (int e = tid; e < cells; e += PM_THREADS) {
-        int t, k;
-        if (axis == 2) {
-            t = e / ng;
-            k = e - t * ng;
-        } else {
-            k = e / tl;
-            t = e - k * tl;
+    return SIGN < 0 ? make_float2(a.y, -a.x) : make_float2(-a.y, a.x);
+}
+
+template <int SIGN>
+__device__ __forceinline__ void dft2(float2 &a, float2 &b)
+{
+    const float2 t = c_sub(a, b);
+    a = c_add(a, b);
+    b = t;
+}
+template <int SIGN>
+__device__ __forceinline__ void dft4(float2 &a, float2 &b, float2 &c, float2 &d)
+{
+    const float2 s0 = c_add(a, c), s1 = c_sub(a, c), s2 = c_add(b, d), s3 = c_quarter<SIGN>(c_sub(b, d));
+    a = c_add(s0, s2);
+    b = c_add(s1, s3);
+    c = c_sub(s0, s2);
+    d = c_sub(s1, s3);
+}
+template <int SIGN>
+__device__ __forceinline__ void dft8(float2 v[8])
+{
+    constexpr float r = 0.70710678118654752f;
+    dft4<SIGN>(v[0], v[2], v[4], v[6]);
+    dft4<SIGN>(v[1], v[3], v[5], v[7]);
+    // odd half times exp(SIGN 2 pi i k / 8)
+    const float2 o1 = make_float2(r * (v[3].x - SIGN * v[3].y), r * (SIGN * v[3].x + v[3].y));
+    const float2 o2 = c_quarter<SIGN>(v[5]);
+    const float2 o3 = make_float2(r * (-v[7].x - SIGN * v[7].y), r * (SIGN * v[7].x - v[7].y));
+    const float2 e0 = v[0], e1 = v[2], e2 = v[4], e3 = v[6], o0 = v[1];
+    v[0] = c_add(e0, o0);
+    v[4] = c_sub(e0, o0);
+    v[1] = c_add(e1, o1);
+    v[5] = c_sub(e1, o1);
+    v[2] = c_add(e2, o2);
+    v[6] = c_sub(e2, o2);
+    v[3] = c_add(e3, o3);
+    v[7] = c_sub(e3, o3);
+}
+
+constexpr int ilog2c(int v) { return v <= 1 ? 0 : 1 + ilog2c(v / 2); }
+
+// The transform of one line: v[q] is point j + q N/8 before and after.  sm: LDS
+// of the block, at(p) the place of point p of this line in it; tw: exp(-2 pi i m / N)
+// in LDS.  Every thread of the block calls this (barriers).  Unnormalised.
+template <int N, int SIGN, typename At>
+__device__ __forceinline__ void fft_line(float2 v[8], int j, float2 *sm, const At &at, const float2 *tw)
+{
+    constexpr int T = N / 8, LG = ilog2c(N), S8 = LG / 3, R = 1 << (LG % 3);
+    auto twid = [&](int m) {
+        const float2 w = tw[m];
+        return SIGN < 0 ? w : make_float2(w.x, -w.y);
+    };
+    int ns = 1;
+#pragma unroll
+    for (int s = 0; s < S8; s++) {
+        if (s > 0) {
+            const int e = (j & (ns - 1)) * (N / (8 * ns));
+#pragma unroll
+            for (int k = 1; k < 8; k++) v[k] = c_mul(v[k], twid(e * k));
         }
-        const int kr = (int)(__brev((unsigned)k) >> (32 - lg));
-        sm[t * ng + kr] = data[base + (size_t)t * lstride + (size_t)k * estride];
+        dft8<SIGN>(v);
+        if (s + 1 < S8 || R > 1) {
+            const int base = (j / ns) * ns * 8 + (j & (ns - 1));
+#pragma unroll
+            for (int k = 0; k < 8; k++) sm[at(base + k * ns)] = v[k];
+            __syncthreads();
+#pragma unroll
+            for (int k = 0; k < 8; k++) v[k] = sm[at(j + k * T)];
+            __syncthreads();
+        }
+        ns *= 8;
+    }
+    if constexpr (R == 2) {
+#pragma unroll
+        for (int m = 0; m < 4; m++) {
+            v[m + 4] = c_mul(v[m + 4], twid(j + m * T));
+            dft2<SIGN>(v[m], v[m + 4]);
+        }
+    } else if constexpr (R == 4) {
+#pragma unroll
+        for (int m = 0; m < 2; m++) {
+            const int b = j + m * T;
+#pragma unroll
+            for (int k = 1; k < 4; k++) v[m + 2 * k] = c_mul(v[m + 2 * k], twid(b * k));
+            dft4<SIGN>(v[m], v[m + 2], v[m + 4], v[m + 6]);
+        }
+    }
+}
+
+// threads of a z pass: 256 / (N / 8) pairs of lines per block
+#define PM_Z_THREADS 256
+
+// Forward along z: rows 2 p and 2 p + 1 of the real mesh as the real and
+// imaginary part of one transform Z; A_k = (Z_k + Z*_{N-k})/2, B_k = (Z_k - Z*_{N-k})/2i.
+template <int N>
+__global__ __launch_bounds__(PM_Z_THREADS) void k_pm_z_forward(const float *__restrict__ real, float2 *__restrict__ half,
+                                                               const float2 *__restrict__ tw)
+{
+    constexpr int T = N / 8, LP = PM_Z_THREADS / T, LINE = N + N / 8 + 1, PZ = pm_pitch(N);
+    __shared__ float2 tws[N], sm[LP * LINE];
+    for (int k = threadIdx.x; k < N; k += PM_Z_THREADS) tws[k] = tw[k];
+    const int t = threadIdx.x / T, j = threadIdx.x % T;
+    const size_t pr = (size_t)blockIdx.x * LP + t;
+    const bool have = pr < (size_t)N * N / 2;
+    const auto at = [&](int p) { return t * LINE + p + (p >> 3); };
+    float2 v[8];
+    const float *r0 = real + (have ? 2 * pr : 0) * N;
+#pragma unroll
+    for (int q = 0; q < 8; q++) v[q] = make_float2(r0[j + q * T], r0[N + j + q * T]);
+    __syncthreads();
+    fft_line<N, -1>(v, j, sm, at, tws);
+#pragma unroll
+    for (int q = 0; q < 8; q++) sm[at(j + q * T)] = v[q];
+    __syncthreads();
+    if (!have) return;
+    float2 *a = half + 2 * pr * PZ, *b = a + PZ;
+#pragma unroll
+    for (int m = 0; m < 5; m++) {
+        const int k = j + m * T;
+        if (m == 4 && j > 0) break;  // k = N / 2 by the first thread
+        const float2 z = sm[at(k)], y = sm[at((N - k) & (N - 1))];
+        a[k] = make_float2(0.5f * (z.x + y.x), 0.5f * (z.y - y.y));
+        b[k] = make_float2(0.5f * (z.y + y.y), 0.5f * (y.x - z.x));
+    }
+}
+
+// Inverse along z: Z = A + i B over the full line from the two half rows (the
+// values at 0 and N / 2 are real), whose transform has line A in its real and line
+// B in its imaginary part.
+template <int N>
+__global__ __launch_bounds__(PM_Z_THREADS) void k_pm_z_inverse(const float2 *__restrict__ half, float *__restrict__ real,
+                                                               const float2 *__restrict__ tw)
+{
+    constexpr int T = N / 8, LP = PM_Z_THREADS / T, LINE = N + N / 8 + 1, PZ = pm_pitch(N);
+    __shared__ float2 tws[N], sm[LP * LINE];
+    for (int k = threadIdx.x; k < N; k += PM_Z_THREADS) tws[k] = tw[k];
+    const int t = threadIdx.x / T, j = threadIdx.x % T;
+    const size_t pr = (size_t)blockIdx.x * LP + t;
+    const bool have = pr < (size_t)N * N / 2;
+    const auto at = [&](int p) { return t * LINE + p + (p >> 3); };
+    const float2 *a = half + (have ? 2 * pr : 0) * PZ, *b = a + PZ;
+    float2 v[8];
+#pragma unroll
+    for (int q = 0; q < 8; q++) {
+        const int k = j + q * T;
+        const bool low = k <= N / 2;
+        const float2 x = a[low ? k : N - k], y = b[low ? k : N - k];
+        if (k == 0 || k == N / 2) v[q] = make_float2(x.x, y.x);
+        else v[q] = low ? make_float2(x.x - y.y, x.y + y.x) : make_float2(x.x + y.y, y.x - x.y);
     }
     __syncthreads();
-    auto cmul = [](float2 a, float2 w) { return make_float2(a.x * w.x - a.y * w.y, a.x * w.y + a.y * w.x); };
-    // radix-2 stages s and s + 1 fused: each thread takes the 4 points
-    // i0, i0 + h, i0 + 2h, i0 + 3h (h = 2^s) through both stages in registers
-    const int qb = ng >> 2;
-    int s = 0;
-    for (; s + 1 < lg; s += 2) {
-        const int half = 1 << s;
-        for (int b = tid; b < tl * qb; b += PM_THREADS) {
-            const int t = b / qb, j = b - t * qb;
-            const int grp = j >> s, pos = j & (half - 1);
-            const int i0 = t * ng + (grp << (s + 2)) + pos;
-            const float2 a0 = sm[i0], a1 = sm[i0 + half], a2 = sm[i0 + 2 * half], a3 = sm[i0 + 3 * half];
-            const float2 w1 = tws[pos << (lg - s - 1)];
-            const float2 b1 = cmul(a1, w1), b3 = cmul(a3, w1);
-            const float2 c0 = make_float2(a0.x + b1.x, a0.y + b1.y), c1 = make_float2(a0.x - b1.x, a0.y - b1.y);
-            const float2 c2 = make_float2(a2.x + b3.x, a2.y + b3.y), c3 = make_float2(a2.x - b3.x, a2.y - b3.y);
-            const float2 d2 = cmul(c2, tws[pos << (lg - s - 2)]), d3 = cmul(c3, tws[(pos + half) << (lg - s - 2)]);
-            sm[i0] = make_float2(c0.x + d2.x, c0.y + d2.y);
-            sm[i0 + 2 * half] = make_float2(c0.x - d2.x, c0.y - d2.y);
-            sm[i0 + half] = make_float2(c1.x + d3.x, c1.y + d3.y);
-            sm[i0 + 3 * half] = make_float2(c1.x - d3.x, c1.y - d3.y);
-        }
-        __syncthreads();
-    }
-    if (s < lg) {  // odd lg: one radix-2 stage left
-        const int half = 1 << s, hb = ng >> 1;
-        for (int b = tid; b < tl * hb; b += PM_THREADS) {
-            const int t = b / hb, j = b - t * hb;
-            const int grp = j >> s, pos = j & (half - 1);
-            const int i0 = t * ng + (grp << (s + 1)) + pos, i1 = i0 + half;
-            const float2 a = sm[i0], bw = cmul(sm[i1], tws[pos << (lg - s - 1)]);
-            sm[i0] = make_float2(a.x + bw.x, a.y + bw.y);
-            sm[i1] = make_float2(a.x - bw.x, a.y - bw.y);
-        }
-        __syncthreads();
-    }
-    for (int e = tid; e < cells; e += PM_THREADS) {
-        int t, k;
-        if (axis == 2) {
-            t = e / ng;
-            k = e - t * ng;
-        } else {
-            k = e / tl;
-            t = e - k * tl;
-        }
-        const size_t o = base + (size_t)t * lstride + (size_t)k * estride;
-        const float2 v = sm[t * ng + k];
-        if (real_out) real_out[o] = v.x;
-        else data[o] = v;
+    fft_line<N, 1>(v, j, sm, at, tws);
+    if (!have) return;
+    float *r0 = real + 2 * pr * N;
+#pragma unroll
+    for (int q = 0; q < 8; q++) {
+        r0[j + q * T] = v[q].x;
+        r0[N + j + q * T] = v[q].y;
     }
 }
 
-// the Green's function with the CIC window deconvolved twice:
-// F(k) = -G (4 pi / V) exp(-k^2 r_s^2) / k^2 / W(k)^2, W = prod_d sinc^2(pi n_d / ng); F(0) = 0
-__global__ void k_pm_green(float2 *__restrict__ mesh, int ng, int lg, double box, double r_s, double G)
+// Lines along y or x of the half spectrum, in place: a block takes PM_COLS lines
+// neighbouring in z, so that every row of the tile is a run of 64 to 128 bytes.
+// MODE 0: forward along y, 1: inverse along y, 2: along x forward, times the
+// Green's function with the CIC window deconvolved twice,
+// F(k) = -G (4 pi / V) exp(-k^2 r_s^2) / k^2 / W(k)^2, W = prod_d sinc^2(pi n_d / N),
+// F(0) = 0, and inverse: the points of a line stay in registers between the two.
+constexpr int pm_cols(int n) { return n >= 1024 ? 8 : 16; }
+
+template <int N, int MODE>
+__global__ __launch_bounds__(pm_cols(N) *N / 8) void k_pm_lines(float2 *__restrict__ half, const float2 *__restrict__ tw,
+                                                               const float *__restrict__ gt, float pref)
 {
-    const size_t ncell = (size_t)ng * ng * ng;
-    const float kf = (float)(2.0 * M_PI / box);
-    const float rs2 = (float)(r_s * r_s);
-    const float pref = (float)(-G * 4.0 * M_PI / (box * box * box));
-    for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < ncell; i += (size_t)gridDim.x * blockDim.x) {
-        const int iz = (int)(i & (size_t)(ng - 1)), iy = (int)((i >> lg) & (size_t)(ng - 1)), ix = (int)(i >> (2 * lg));
-        const int nx = ix < ng / 2 ? ix : ix - ng, ny = iy < ng / 2 ? iy : iy - ng, nz = iz < ng / 2 ? iz : iz - ng;
-        if (nx == 0 && ny == 0 && nz == 0) {
-            mesh[i] = make_float2(0.f, 0.f);
-            continue;
-        }
-        const float kx = kf * nx, ky = kf * ny, kz = kf * nz;
-        const float k2 = kx * kx + ky * ky + kz * kz;
-        float W = 1.f;
-        const int nn[3] = {nx, ny, nz};
+    constexpr int T = N / 8, TL = pm_cols(N), NZ = N / 2 + 1, PZ = pm_pitch(N), TILES = (NZ + TL - 1) / TL;
+    __shared__ float2 tws[N], sm[(N + N / 8) * TL];
+    for (int k = threadIdx.x; k < N; k += TL * T) tws[k] = tw[k];
+    const int t = threadIdx.x % TL, j = threadIdx.x / TL;
+    const int outer = blockIdx.x / TILES, z = (blockIdx.x % TILES) * TL + t;
+    const bool have = z < NZ;
+    const auto at = [&](int p) { return (p + (p >> 3)) * TL + t; };
+    // y: rows outer N + p; x: rows p N + outer
+    const size_t stride = MODE == 2 ? (size_t)N * PZ : (size_t)PZ;
+    float2 *line = half + (MODE == 2 ? (size_t)outer * PZ : (size_t)outer * N * PZ) + (have ? z : 0);
+    float2 v[8];
 #pragma unroll
-        for (int d = 0; d < 3; d++) {
-            if (nn[d]) {
-                const float u = (float)M_PI * (float)nn[d] / (float)ng;
-                const float sc = sinf(u) / u;
-                W *= sc * sc;
-            }
+    for (int q = 0; q < 8; q++) v[q] = line[(size_t)(j + q * T) * stride];
+    __syncthreads();
+    if constexpr (MODE == 0) fft_line<N, -1>(v, j, sm, at, tws);
+    if constexpr (MODE == 1) fft_line<N, 1>(v, j, sm, at, tws);
+    if constexpr (MODE == 2) {
+        fft_line<N, -1>(v, j, sm, at, tws);
+        const int ny = outer < N / 2 ? outer : outer - N;
+        const float gyz = gt[outer] * gt[have ? z : 0] * pref;
+        const int n2 = ny * ny + z * z;
+#pragma unroll
+        for (int q = 0; q < 8; q++) {
+            const int ix = j + q * T, nx = ix < N / 2 ? ix : ix - N;
+            const int k2 = nx * nx + n2;
+            const float f = k2 ? gyz * gt[ix] / (float)k2 : 0.f;
+            v[q].x *= f;
+            v[q].y *= f;
         }
-        const float f = pref * expf(-k2 * rs2) / (k2 * W * W);
-        const float2 v = mesh[i];
-        mesh[i] = make_float2(v.x * f, v.y * f);
+        fft_line<N, 1>(v, j, sm, at, tws);
     }
+    if (!have) return;
+#pragma unroll
+    for (int q = 0; q < 8; q++) line[(size_t)(j + q * T) * stride] = v[q];
+}
+
+// real mesh -> real potential, through the half spectrum
+template <int N>
+static void pm_potential(float *real, float2 *half, const float2 *tw, const float *gt, float pref, hipStream_t s)
+{
+    constexpr int T = N / 8, LP = PM_Z_THREADS / T, TL = pm_cols(N), TILES = (N / 2 + 1 + TL - 1) / TL;
+    const unsigned zb = (unsigned)(((size_t)N * N / 2 + LP - 1) / LP), lb = (unsigned)N * TILES;
+    k_pm_z_forward<N><<<zb, PM_Z_THREADS, 0, s>>>(real, half, tw);
+    k_pm_lines<N, 0><<<lb, TL * T, 0, s>>>(half, tw, gt, pref);
+    k_pm_lines<N, 2><<<lb, TL * T, 0, s>>>(half, tw, gt, pref);
+    k_pm_lines<N, 1><<<lb, TL * T, 0, s>>>(half, tw, gt, pref);
+    k_pm_z_inverse<N><<<zb, PM_Z_THREADS, 0, s>>>(half, real, tw);
 }
 
 // gradient (4th-order differences) and CIC interpolation, one particle per thread
@@ -277,11 +393,28 @@ static int ilog2(int v)
     return g;
 }
 
-int g4_pm_layout_bytes(int ng, size_t *bytes)
+// real mesh (density, then potential), half spectrum, tables
+struct PmLayout {
+    size_t real, half, tw, gt, total;
+};
+static int pm_layout(int ng, PmLayout *L)
 {
     if (ng < 8 || ng > 1024 || (ng & (ng - 1))) return G4_EINVAL;
+    auto al = [](size_t b) { return (b + 255) / 256 * 256; };
     const size_t ncell = (size_t)ng * ng * ng;
-    *bytes = ((size_t)ng / 2 * 8 + 255) / 256 * 256 + (ncell * 8 + 255) / 256 * 256 + (ncell * 4 + 255) / 256 * 256;
+    L->real = 0;
+    L->half = al(ncell * 4);
+    L->tw = L->half + al((size_t)ng * ng * pm_pitch(ng) * 8);
+    L->gt = L->tw + al((size_t)ng * 8);
+    L->total = std::max(L->gt + al((size_t)ng * 4), al((size_t)ng / 2 * 8) + al(ncell * 8) + al(ncell * 4));
+    return G4_OK;
+}
+
+int g4_pm_layout_bytes(int ng, size_t *bytes)
+{
+    PmLayout L;
+    if (pm_layout(ng, &L)) return G4_EINVAL;
+    *bytes = L.total;
     return G4_OK;
 }
 
@@ -289,32 +422,33 @@ int g4_launch_pm(g4_ctx *ctx, const g4_tree *t, const g4_pm_params *pp, void *ws
                  double *ax, double *ay, double *az, double *pot)
 {
     const int ng = pp->ng, lg = ilog2(ng);
-    size_t need = 0;
-    if (g4_pm_layout_bytes(ng, &need)) return g4_set_err(ctx, G4_EINVAL, "ng must be a power of two in [8, 1024]");
-    if (ws_bytes < need) return g4_set_err(ctx, G4_ENOMEM, "pm workspace too small");
+    PmLayout L;
+    if (pm_layout(ng, &L)) return g4_set_err(ctx, G4_EINVAL, "ng must be a power of two in [8, 1024]");
+    if (ws_bytes < L.total) return g4_set_err(ctx, G4_ENOMEM, "pm workspace too small");
     char *b = (char *)ws;
     const size_t ncell = (size_t)ng * ng * ng;
-    float2 *tw = (float2 *)b;
-    b += ((size_t)ng / 2 * 8 + 255) / 256 * 256;
-    float2 *mesh = (float2 *)b;
-    b += (ncell * 8 + 255) / 256 * 256;
-    float *phi = (float *)b;
+    float *phi = (float *)(b + L.real), *gt = (float *)(b + L.gt);
+    float2 *half = (float2 *)(b + L.half), *tw = (float2 *)(b + L.tw);
     hipStream_t s = ctx->stream;
     const int shift = 32 - lg;
     const float wscale = ldexpf(1.f, -shift);
-    k_pm_twiddle<<<(ng / 2 + 255) / 256, 256, 0, s>>>(tw, ng);
-    k_pm_clear<<<4096, 256, 0, s>>>(mesh, ncell);
+    k_pm_tables<<<(ng + 255) / 256, 256, 0, s>>>(tw, gt, ng, t->tp.box, pp->r_s);
+    k_pm_clear<<<(unsigned)std::min<size_t>(4096, (ncell / 4 + 255) / 256), 256, 0, s>>>((float4 *)phi, ncell / 4);
     const int64_t n = t->n;
     const unsigned pblocks = (unsigned)std::min<int64_t>(8192, (n + 255) / 256);
-    k_pm_deposit<<<pblocks, 256, 0, s>>>(t->parts, n, ng, shift, wscale, mesh);
-    const int tl = std::min(ng, std::max(1, PM_TILE_CELLS / ng));
-    const unsigned tiles = (unsigned)((size_t)ng * ng / tl);
-    const size_t lds = ((size_t)tl * ng + ng / 2) * sizeof(float2);
-    for (int axis = 2; axis >= 0; axis--)
-        k_pm_fft<<<tiles, PM_THREADS, lds, s>>>(mesh, tw, ng, lg, tl, axis, -1.f, nullptr);
-    k_pm_green<<<4096, 256, 0, s>>>(mesh, ng, lg, t->tp.box, pp->r_s, pp->G);
-    for (int axis = 0; axis <= 2; axis++)
-        k_pm_fft<<<tiles, PM_THREADS, lds, s>>>(mesh, tw, ng, lg, tl, axis, 1.f, axis == 2 ? phi : nullptr);
+    k_pm_deposit<<<pblocks, 256, 0, s>>>(t->parts, n, ng, shift, wscale, phi);
+    // -G 4 pi / V / (2 pi / L)^2: the sum over wave numbers in units of 2 pi / L
+    const float pref = (float)(-pp->G / (M_PI * t->tp.box));
+    switch (lg) {
+    case 3: pm_potential<8>(phi, half, tw, gt, pref, s); break;
+    case 4: pm_potential<16>(phi, half, tw, gt, pref, s); break;
+    case 5: pm_potential<32>(phi, half, tw, gt, pref, s); break;
+    case 6: pm_potential<64>(phi, half, tw, gt, pref, s); break;
+    case 7: pm_potential<128>(phi, half, tw, gt, pref, s); break;
+    case 8: pm_potential<256>(phi, half, tw, gt, pref, s); break;
+    case 9: pm_potential<512>(phi, half, tw, gt, pref, s); break;
+    default: pm_potential<1024>(phi, half, tw, gt, pref, s); break;
+    }
     const float inv_h = (float)(ng / t->tp.box);
     k_pm_interp<<<pblocks, 256, 0, s>>>(t->parts, t->perm1, n, phi, ng, lg, shift, wscale, inv_h, accumulate, ax,
                                         ay, az, pot);
