@@ -86,8 +86,8 @@ typedef struct {
  *            always opened.  TreePM drops nodes whose nearest edge is farther
  *            than r_cut.  alpha_split = 1/(2 r_s).
  * group_size: most particles per 64-lane wavefront group (1..64; 0: 64).
- *            Small sets are walked in smaller groups (sqrt(n)/22, at least
- *            2) so that the chip is filled; results do not depend on it.
+ *            Small sets are walked in smaller groups (sqrt(n)/16, at least
+ *            8) so that the chip is filled; results do not depend on it.
  * a_seed:    device, caller order, |a| per particle (nullable).
  * seed_from_tree: with a_seed NULL, 1 = use the |a| that the previous
  *            geometric (criterion 0) call left in this tree instead of
