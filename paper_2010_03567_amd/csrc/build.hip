@@ -8,12 +8,10 @@
 // Sec. "One-sided multipole expansion" (moments about the centre of mass),
 // Sec. "Fast multipole method" first phase (moments from daughter moments).
 //
-// Design: every kernel is a grid-stride loop whose trip count is read from
-// device counters, so the whole build is enqueued without a host round trip.
-// Nodes of level l+1 are allocated by atomics while level l is processed;
-// each level therefore occupies one contiguous index range.  Allocation order
-// inside a level varies run to run, results do not: traversal and moment
-// sums follow each node's own children in octant order.
+// Design: the build is enqueued without a host round trip; sizes that only the
+// device knows are read there.  The nodes of all levels are found from the
+// sorted keys at once (see "nodes"); each level occupies one contiguous index
+// range, in curve order.  Multipoles go level by level from the deepest up.
 #include <cstring>
 #include <utility>
 
@@ -202,24 +200,6 @@ __global__ void k_gather(const uint4 *__restrict__ pk, const uint32_t *__restric
 // particle, the records 16)
 static inline uint4 *packed_staging(g4_tree *t) { return reinterpret_cast<uint4 *>(t->mom); }
 
-__global__ void k_init(DevCounters *C, uint32_t *bfirst, uint32_t *bcount, uint32_t *parent, uint32_t n)
-{
-    if (threadIdx.x == 0 && blockIdx.x == 0) {
-        C->node_count = 1;
-        C->flags = 0;
-        for (int l = 0; l < G4_MAXLEV + 4; l++) {
-            C->lvl_start[l] = 0;
-            C->lvl_count[l] = 0;
-        }
-        C->lvl_start[0] = 0;
-        C->lvl_count[0] = 1;
-        for (int s = 0; s < 18; s++) C->stat[s] = 0;
-        bfirst[0] = 0;
-        bcount[0] = n;
-        parent[0] = 0xffffffffu;
-    }
-}
-
 // sum over the eight lanes of a group; every lane ends with the same bits
 template <typename T>
 __device__ __forceinline__ T grp8_sum(T v)
@@ -230,251 +210,271 @@ __device__ __forceinline__ T grp8_sum(T v)
     return v;
 }
 
-// nodes up to this many particles find their octant boundaries by one
-// strided pass over their keys instead of a search
-static constexpr uint32_t kScanMax = 256;
-// blocks of the split passes: one per compute unit keeps the number of
-// same-address atomics per level at most this
-static constexpr int kSplitBlocks = 256;
-
-// Process the nodes of one level: a node with more than B particles (and
-// above the depth cap) gets its non-empty octants as children, delimited by
-// the octant digit boundaries in its sorted key range.
+// ------------------------------------------------------------------ nodes
+// All levels of the octree at once, from the sorted keys.  With
+//   d(i) = common leading octants of the keys of particles i - 1 and i (-1 where
+//          a box starts) and
+//   D(i) = the largest number of common octants of any B + 1 consecutive
+//          particles around i (-1 if there are none),
+// the level-l cell of particle i starts at i iff d(i) < l, and holds more than B
+// particles iff l <= D(i); so the leaf of i is at level L(i) = min(D(i) + 1, max
+// depth), and the nodes that start at i are those of levels d(i) + 1 .. L(i).
+// A node's number is its level's base plus the count of earlier starts of that
+// level (nodes of a level are in curve order, the children of a node
+// consecutive); the particle that ends a cell, d(j) < l <= L(j - 1), knows the
+// end and the last child of the node before it.
 //
-// A block takes a slice of the level's nodes (the level spread evenly over
-// the grid) and works in four steps, with block barriers between them:
-//  1. one thread per node: leaf records are written, the nodes to split are
-//     listed in LDS, small (<= kScanMax particles) and large apart;
-//  2. octant starts: a small node by a group of eight lanes, which count its
-//     octant digits in one strided pass (loads that do not wait on each
-//     other); a large node by a whole wavefront, eight lanes per boundary
-//     running a 9-ary search (log_9 of the size rounds of dependent loads
-//     rather than log_2: the top levels hold nodes of millions of keys);
-//  3. child counts, an exclusive scan over the block, and ONE atomic on the
-//     level's counter for the block's children (same-address atomics are
-//     serialised chip-wide, about 11 ns each, so one per node or per
-//     wavefront would cost more than all the searches);
-//  4. one thread per split node writes its children and its record.
-// An empty level returns at once and writes nothing; the node count is
-// summed from the level sizes after the last level.
+// Four launches in place of one per level: k_levels (d, L, starts per block and
+// level), k_level_scan, k_emit, k_records.  Bound by reading the keys; a level by
+// level split cost a launch and a chain of dependent loads per level, 22 of them:
+// 0.89 -> 0.41 ms at 2^24 particles (leaf 32), 0.09 -> 0.02 ms at 8192 (leaf 8).
+#define LV_TILE 1024          // particles per block, one per thread
+#define LV_WAVES (LV_TILE / 64)
+#define LV_MAXB 1024          // leaf sizes whose windows fit the block's LDS
+#define NLEV (G4_MAXLEV + 1)
 
-// nodes a block takes per pass (LDS lists and octant starts are sized for it)
-#define SPLIT_CHUNK 1024
-
-__device__ __forceinline__ void node_record(DevCounters *C, const uint4 *__restrict__ parts, WNode *__restrict__ wn,
-                                            uint32_t q, uint32_t first, uint32_t count, bool split, uint32_t c0,
-                                            uint32_t nch, int level, int B, int S, uint32_t corner)
+// common leading octants of two 63-bit keys
+__device__ __forceinline__ int common_octants(uint64_t a, uint64_t b)
 {
-    // the geometric centre of the cube from any particle inside it
-    const uint4 p0 = parts[first];
-    const int sh = S - level;
-    WNode w;
-    uint32_t pc[3] = {p0.x, p0.y, p0.z}, g[3];
-    for (int k = 0; k < 3; k++) {
-        uint64_t rel = (uint64_t)(uint32_t)(pc[k] - corner);
-        g[k] = (uint32_t)((uint64_t)corner + ((rel >> sh) << sh) + (1ull << (sh - 1)));
-    }
-    w.gx = g[0];
-    w.gy = g[1];
-    w.gz = g[2];
-    w.cx = g[0];
-    w.cy = g[1];
-    w.cz = g[2];
-    w.mass = 0.f;
-    for (int k = 0; k < 6; k++) w.q[k] = 0.f;
-    if (split) {
-        w.next = c0;
-        w.num = nch;
-        w.meta = (uint32_t)level;
+    const uint64_t x = a ^ b;
+    return x ? (__builtin_clzll(x) - 1) / 3 : G4_MAXLEV;
+}
+
+// 1 + common octants of particles s and s + B (0: not both in one box)
+__device__ __forceinline__ uint32_t window_octants(const uint64_t *__restrict__ keys, const uint32_t *__restrict__ box,
+                                                   int64_t s, int64_t n, int64_t B)
+{
+    if (s < 0 || s + B >= n || (box && box[s] != box[s + B])) return 0u;
+    return 1u + (uint32_t)common_octants(keys[s], keys[s + B]);
+}
+
+// bits lo .. hi (none if lo > hi)
+__device__ __forceinline__ uint32_t level_bits(int lo, int hi) { return lo > hi ? 0u : (2u << hi) - (1u << lo); }
+
+// or of the 64 lanes' masks (uniform)
+__device__ __forceinline__ uint32_t wave_or(uint32_t m)
+{
+    for (int off = 32; off > 0; off >>= 1) m |= (uint32_t)__shfl_xor((int)m, off);
+    return (uint32_t)__builtin_amdgcn_readfirstlane((int)m);
+}
+
+// for leaf sizes beyond LV_MAXB: windows in memory, and their running maxima by
+// doubling (out[i] = max(in[i], in[i - step]))
+__global__ void k_window(const uint64_t *__restrict__ keys, const uint32_t *__restrict__ box, int64_t n, int64_t B,
+                         uint8_t *__restrict__ out)
+{
+    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
+        out[i] = (uint8_t)window_octants(keys, box, i, n, B);
+}
+__global__ void k_window_max(const uint8_t *__restrict__ in, int64_t n, int64_t step, uint8_t *__restrict__ out)
+{
+    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
+        out[i] = i >= step && in[i - step] > in[i] ? in[i - step] : in[i];
+}
+
+// lev[i] = (d(i) + 1) | L(i) << 8, and the starts of every level per block
+// (cnt[level][block]).  wmax: 1 + D(i) already in memory, or null.
+__global__ __launch_bounds__(LV_TILE) void k_levels(const uint64_t *__restrict__ keys, const uint32_t *__restrict__ box,
+                                                    const uint8_t *__restrict__ wmax, int64_t n, int64_t B, int maxd,
+                                                    uint16_t *__restrict__ lev, uint32_t *__restrict__ cnt, uint32_t nblk)
+{
+    __shared__ uint8_t w[2][LV_TILE + LV_MAXB];
+    __shared__ uint32_t total[NLEV];
+    const int64_t base = blockIdx.x * (int64_t)LV_TILE, i = base + threadIdx.x;
+    if (threadIdx.x < NLEV) total[threadIdx.x] = 0;
+    uint32_t top = 0;  // 1 + D(i)
+    if (wmax) {
+        if (i < n) top = wmax[i];
+        __syncthreads();
     } else {
-        w.next = first;
-        w.num = count;
-        w.meta = (uint32_t)level | WN_LEAF;
-        if (count > (uint32_t)B) atomicOr(&C->flags, 1u);
-    }
-    wn[q] = w;
-}
-
-// Start of octant d = lane % 8 of a node of at most kScanMax particles, by
-// the group of eight lanes holding `lane` (all eight call this): histogram of
-// the octant digits over a strided pass (16-bit fields, two words), then
-// prefix sums. The loads go out eight at a time (clamped indices, no
-// branches), so a batch costs one trip to memory rather than eight.
-__device__ __forceinline__ uint32_t group_octant_start(const uint64_t *__restrict__ keys, uint32_t first,
-                                                       uint32_t count, uint32_t lane, int shift)
-{
-    const uint32_t d = lane & 7, stop = first + count;
-    uint64_t h03 = 0, h47 = 0;
-    for (uint32_t j0 = first + d; j0 < stop; j0 += 64) {
-        uint64_t kv[8];
-#pragma unroll
-        for (uint32_t u = 0; u < 8; u++) {
-            const uint32_t j = j0 + 8 * u;
-            kv[u] = keys[j < stop ? j : stop - 1];
-        }
-#pragma unroll
-        for (uint32_t u = 0; u < 8; u++) {
-            const uint32_t e = (uint32_t)(kv[u] >> shift) & 7u;
-            const uint64_t one = j0 + 8 * u < stop ? 1ull << (16 * (e & 3)) : 0ull;
-            if (e < 4) h03 += one;
-            else h47 += one;
-        }
-    }
-    h03 = grp8_sum(h03);
-    h47 = grp8_sum(h47);
-    uint32_t lo = first;
-    for (uint32_t e = 0; e < 8; e++) {
-        const uint32_t he = (uint32_t)(((e < 4 ? h03 : h47) >> (16 * (e & 3))) & 0xffffu);
-        if (e < d) lo += he;
-    }
-    return lo;
-}
-
-// Start of octant b = lane / 8 of a large node, by the whole wavefront (all
-// 64 lanes call this). Lane (b, k) keeps the search range [lo, hi] of the
-// first key with digit >= b and probes position k + 1 of 9 in it; the eight
-// answers narrow the range to a ninth. Every lane of group b returns it.
-__device__ __forceinline__ uint32_t wave_octant_start(const uint64_t *__restrict__ keys, uint32_t first,
-                                                      uint32_t count, uint32_t lane, int shift)
-{
-    const uint32_t b = lane >> 3, k = lane & 7, stop = first + count;
-    const uint64_t target = ((keys[first] >> (shift + 3)) << (shift + 3)) | ((uint64_t)b << shift);
-    // octant 0 starts at the node's first key; the others are searched in [first, stop]
-    uint32_t lo = first, hi = b == 0 ? first : stop;
-    while (__ballot(hi > lo) != 0ull) {
-        const uint32_t len = hi - lo;
-        const uint32_t pos = lo + (uint32_t)(((uint64_t)len * (k + 1)) / 9u);
-        const bool less = len > 0 && keys[pos] < target;
-        const uint32_t c = __popc((uint32_t)(__ballot(less) >> (lane & 56)) & 0xffu);
-        // the probes below target form a prefix; the boundary is in (probe c-1, probe c]
-        const uint32_t p_lo = __shfl(pos, (int)((lane & 56) + (c > 0 ? c - 1 : 0)));
-        const uint32_t p_hi = __shfl(pos, (int)((lane & 56) + (c < 8 ? c : 7)));
-        if (len > 0) {
-            if (c > 0) lo = p_lo + 1;
-            if (c < 8) hi = p_hi;
-        }
-    }
-    return lo;
-}
-
-__global__ __launch_bounds__(256) void k_split(DevCounters *C, const uint64_t *__restrict__ keys,
-                                               const uint4 *__restrict__ parts, uint32_t *__restrict__ bfirst,
-                                               uint32_t *__restrict__ bcount, uint32_t *__restrict__ parent,
-                                               WNode *__restrict__ wn, int level, int B, int maxd, int S,
-                                               uint32_t corner, int64_t cap)
-{
-    // the pass's split nodes: small ones from the front, large ones from the back
-    __shared__ uint32_t s_node[SPLIT_CHUNK];
-    // entry i (small nodes first, then large): octant starts and end of the node
-    __shared__ uint32_t s_start[SPLIT_CHUNK][8];
-    __shared__ uint32_t s_stop[SPLIT_CHUNK];
-    __shared__ uint32_t s_off[SPLIT_CHUNK];  // first child of entry i, relative to the block's base
-    __shared__ uint32_t s_ctr[2], s_wsum[4], s_base;
-    // level l is complete (pass l-1 has finished); level l+1 starts right after it
-    const uint32_t beg = C->lvl_start[level], end = beg + C->lvl_count[level];
-    if (beg == end) return;
-    if (blockIdx.x == 0 && threadIdx.x == 0) C->lvl_start[level + 1] = end;
-    const uint32_t t = threadIdx.x, lane = t & 63, wv = t >> 6;
-    const uint32_t cnt = end - beg;
-    const int shift = 3 * (G4_MAXLEV - level - 1);
-    uint32_t per = (cnt + gridDim.x - 1) / gridDim.x;
-    if (per > SPLIT_CHUNK) per = SPLIT_CHUNK;
-    for (uint64_t pass = blockIdx.x; pass * per < cnt; pass += gridDim.x) {
-        const uint32_t cb = beg + (uint32_t)(pass * per), ce = min(cb + per, end);
-        if (t < 2) s_ctr[t] = 0;
+        // window maxima over [i - B, i] by doubling, from B particles before the tile on
+        const int len = LV_TILE + (int)B;
+        for (int k = threadIdx.x; k < len; k += LV_TILE) w[0][k] = (uint8_t)window_octants(keys, box, base - B + k, n, B);
         __syncthreads();
-        // 1. leaves and the list of nodes to split
-        for (uint32_t q = cb + t; q < ce; q += 256) {
-            const uint32_t first = bfirst[q], count = bcount[q];
-            const bool split = count > (uint32_t)B && level < maxd;
-            if (!split) node_record(C, parts, wn, q, first, count, false, 0, 0, level, B, S, corner);
-            else if (count <= kScanMax) s_node[atomicAdd(&s_ctr[0], 1u)] = q;
-            else s_node[SPLIT_CHUNK - 1 - atomicAdd(&s_ctr[1], 1u)] = q;
-        }
-        __syncthreads();
-        const uint32_t ns = s_ctr[0], nl = s_ctr[1], nsplit = ns + nl;
-        // 2. octant starts
-        for (uint32_t i0 = 0; i0 < ns; i0 += 32) {
-            const uint32_t i = i0 + (t >> 3);
-            if (i < ns) {
-                const uint32_t q = s_node[i], first = bfirst[q], count = bcount[q];
-                s_start[i][lane & 7] = group_octant_start(keys, first, count, lane, shift);
-                if ((lane & 7) == 0) s_stop[i] = first + count;
+        int cur = 0, span = 1;
+        for (; 2 * span <= (int)B + 1; span *= 2) {
+            for (int k = threadIdx.x; k < len; k += LV_TILE) {
+                const uint8_t a = w[cur][k], b = k >= span ? w[cur][k - span] : (uint8_t)0;
+                w[cur ^ 1][k] = a > b ? a : b;
             }
+            cur ^= 1;
+            __syncthreads();
         }
-        for (uint32_t k = wv; k < nl; k += 4) {
-            const uint32_t q = s_node[SPLIT_CHUNK - 1 - k], first = bfirst[q], count = bcount[q];
-            const uint32_t lo = wave_octant_start(keys, first, count, lane, shift);
-            if ((lane & 7) == 0) s_start[ns + k][lane >> 3] = lo;
-            if (lane == 0) s_stop[ns + k] = first + count;
-        }
-        __syncthreads();
-        // 3. child counts (four entries a thread), block scan, one atomic
-        uint32_t nc[4], sum = 0;
-#pragma unroll
-        for (uint32_t u = 0; u < 4; u++) {
-            const uint32_t i = 4 * t + u;
-            nc[u] = 0;
-            if (i < nsplit)
-                for (uint32_t d = 0; d < 8; d++) nc[u] += (d < 7 ? s_start[i][d + 1] : s_stop[i]) > s_start[i][d];
-            sum += nc[u];
-        }
-        uint32_t incl = sum;
+        const int k = (int)B + threadIdx.x;
+        top = max((uint32_t)w[cur][k], (uint32_t)w[cur][k - ((int)B + 1 - span)]);
+    }
+    int d1 = NLEV + 1, L = 0;  // d + 1 and L; past the end nothing starts
+    if (i < n) {
+        d1 = i == 0 || (box && box[i] != box[i - 1]) ? 0 : 1 + common_octants(keys[i - 1], keys[i]);
+        L = min((int)top, maxd);
+        lev[i] = (uint16_t)(d1 | L << 8);
+    }
+    for (uint32_t m = wave_or(level_bits(d1, L)); m; m &= m - 1) {  // the few levels that start among 64 neighbours
+        const int l = __builtin_ctz(m);
+        const uint32_t c = (uint32_t)__builtin_popcountll(__builtin_amdgcn_ballot_w64(d1 <= l && l <= L));
+        if ((threadIdx.x & 63) == 0) atomicAdd(&total[l], c);
+    }
+    __syncthreads();
+    if (threadIdx.x < NLEV) cnt[(size_t)threadIdx.x * nblk + blockIdx.x] = total[threadIdx.x];
+}
+
+// exclusive scan of one level's block counts (block = level), its size; block 0 resets the tree's counters
+__global__ __launch_bounds__(1024) void k_level_scan(uint32_t *__restrict__ cnt, uint32_t nblk, DevCounters *__restrict__ C)
+{
+    __shared__ uint32_t wsum[16];
+    uint32_t *row = cnt + (size_t)blockIdx.x * nblk;
+    const uint32_t lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    uint32_t carry = 0;
+    for (uint32_t c0 = 0; c0 < nblk; c0 += 1024) {
+        const uint32_t k = c0 + threadIdx.x, x = k < nblk ? row[k] : 0u;
+        uint32_t incl = x;
 #pragma unroll
         for (uint32_t off = 1; off < 64; off <<= 1) {
             const uint32_t y = __shfl_up(incl, off);
             if (lane >= off) incl += y;
         }
-        if (lane == 63) s_wsum[wv] = incl;
+        if (lane == 63) wsum[wv] = incl;
         __syncthreads();
-        uint32_t before = incl - sum, total = 0;
-        for (uint32_t w = 0; w < 4; w++) {
-            before += w < wv ? s_wsum[w] : 0u;
-            total += s_wsum[w];
+        uint32_t before = carry, all = carry;
+        for (uint32_t v = 0; v < 16; v++) {
+            before += v < wv ? wsum[v] : 0u;
+            all += wsum[v];
         }
-#pragma unroll
-        for (uint32_t u = 0; u < 4; u++) {
-            const uint32_t i = 4 * t + u;
-            if (i < nsplit) s_off[i] = before;
-            before += nc[u];
-        }
-        if (t == 0) s_base = total ? atomicAdd(&C->lvl_count[level + 1], total) : 0u;
-        __syncthreads();
-        // 4. children and records of the split nodes
-        for (uint32_t i = t; i < nsplit; i += 256) {
-            const uint32_t q = i < ns ? s_node[i] : s_node[SPLIT_CHUNK - 1 - (i - ns)];
-            const uint32_t first = s_start[i][0], stop = s_stop[i];
-            const uint32_t c0 = end + s_base + s_off[i];
-            uint32_t nch = 0;
-            for (uint32_t d = 0; d < 8; d++) nch += (d < 7 ? s_start[i][d + 1] : stop) > s_start[i][d];
-            const bool fits = (int64_t)c0 + nch <= cap;
-            if (fits) {
-                uint32_t c = c0;
-                for (uint32_t d = 0; d < 8; d++) {
-                    const uint32_t lo = s_start[i][d], hi = d < 7 ? s_start[i][d + 1] : stop;
-                    if (hi > lo) {
-                        bfirst[c] = lo;
-                        bcount[c] = hi - lo;
-                        parent[c] = q;
-                        c++;
-                    }
-                }
-            } else {
-                atomicOr(&C->flags, 2u);
-            }
-            node_record(C, parts, wn, q, first, stop - first, fits, c0, nch, level, B, S, corner);
-        }
+        if (k < nblk) row[k] = before + incl - x;
+        carry = all;
         __syncthreads();
     }
+    if (threadIdx.x == 0) C->lvl_count[blockIdx.x] = carry;
+    if (blockIdx.x == 0 && threadIdx.x < 18) C->stat[threadIdx.x] = 0;
+    if (blockIdx.x == 0 && threadIdx.x == 0) C->flags = 0;
+    if (blockIdx.x == 0 && threadIdx.x >= NLEV && threadIdx.x < G4_MAXLEV + 4) C->lvl_count[threadIdx.x] = 0;
 }
 
-// node count = the sum of the level sizes (after the last split pass)
-__global__ void k_count_nodes(DevCounters *C)
+__global__ __launch_bounds__(LV_TILE) void k_emit(const uint16_t *__restrict__ lev, int64_t n, int maxd,
+                                                  const uint32_t *__restrict__ cnt, uint32_t nblk,
+                                                  DevCounters *__restrict__ C, uint32_t *__restrict__ bfirst,
+                                                  uint32_t *__restrict__ bend, uint32_t *__restrict__ parent,
+                                                  uint32_t *__restrict__ cfirst, uint32_t *__restrict__ cend, int64_t cap)
 {
-    if (threadIdx.x == 0 && blockIdx.x == 0) {
-        uint32_t s = 0;
-        for (int l = 0; l < G4_MAXLEV + 1; l++) s += C->lvl_count[l];
-        C->node_count = s;
+    __shared__ uint32_t off[NLEV][LV_WAVES];  // starts per wavefront, then the number of its first one
+    const int64_t i = blockIdx.x * (int64_t)LV_TILE + threadIdx.x;
+    const uint32_t lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    int d1 = NLEV + 1, L = 0, Lp = 0;  // Lp: leaf level of particle i - 1
+    if (i < n) {
+        const uint16_t v = lev[i];
+        d1 = v & 0xff;
+        L = v >> 8;
+        Lp = i > 0 ? lev[i - 1] >> 8 : -1;
+    }
+    if (lane < NLEV) off[lane][wv] = 0;
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    const bool last = i == n - 1;
+    const uint32_t ms = wave_or(level_bits(d1, L));
+    for (uint32_t m = ms; m; m &= m - 1) {
+        const int l = __builtin_ctz(m);
+        const uint32_t c = (uint32_t)__builtin_popcountll(__builtin_amdgcn_ballot_w64(d1 <= l && l <= L));
+        if (lane == 0) off[l][wv] = c;
+    }
+    // levels to go through: those that start or end here, the ones above (parents) and below (last children)
+    uint32_t mt = ms | wave_or(level_bits(d1, Lp) | (last ? level_bits(0, L) : 0u));
+    mt = (mt | mt >> 1 | mt << 1) & level_bits(0, maxd);
+    __syncthreads();
+    if (threadIdx.x <= (unsigned)maxd) {
+        const uint32_t l = threadIdx.x;
+        uint32_t run = 0;
+        for (uint32_t k = 0; k < l; k++) run += C->lvl_count[k];  // the level's base
+        if (blockIdx.x == 0) {
+            const uint32_t size = C->lvl_count[l];
+            C->lvl_start[l] = run;
+            if (l == (uint32_t)maxd) C->node_count = (uint32_t)min((int64_t)run + size, cap);
+        }
+        run += cnt[(size_t)l * nblk + blockIdx.x];
+        for (uint32_t w = 0; w < LV_WAVES; w++) {
+            const uint32_t c = off[l][w];
+            off[l][w] = run;
+            run += c;
+        }
+    }
+    __syncthreads();
+    uint32_t up = 0xffffffffu;  // node of the level above that holds particle i
+    bool up_starts = false;
+    uint32_t closed = 0xffffffffu;  // node of the level above that ends before particle i
+    bool over = false;
+    auto put = [&](uint32_t *a, uint32_t q, uint32_t v) {
+        if ((int64_t)q < cap) a[q] = v;
+        else over = true;
+    };
+    for (; mt; mt &= mt - 1) {
+        const int l = __builtin_ctz(mt);
+        const bool starts = d1 <= l && l <= L;
+        const uint64_t m = __builtin_amdgcn_ballot_w64(starts);
+        const uint32_t q = off[l][wv] + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+        if (i >= n) continue;
+        if (closed != 0xffffffffu) put(cend, closed, q);  // its children end where the next ones start
+        closed = 0xffffffffu;
+        if (d1 <= l && l <= Lp) {
+            closed = q - 1;
+            put(bend, closed, (uint32_t)i);
+        }
+        if (starts) {
+            put(bfirst, q, (uint32_t)i);
+            put(parent, q, up);
+            if (up_starts) put(cfirst, up, q);
+        }
+        const uint32_t here = q + (starts ? 1u : 0u) - 1u;
+        if (last && l <= L) put(bend, here, (uint32_t)n);
+        if (last && l > 0 && l - 1 <= L) put(cend, up, here + 1u);
+        up = here;
+        up_starts = starts;
+    }
+    if (over) atomicOr(&C->flags, 2u);
+}
+
+__global__ void k_records(DevCounters *__restrict__ C, const uint16_t *__restrict__ lev, const uint4 *__restrict__ parts,
+                          const uint32_t *__restrict__ bfirst, uint32_t *__restrict__ bcount,
+                          const uint32_t *__restrict__ cfirst, const uint32_t *__restrict__ cend, WNode *__restrict__ wn,
+                          int B, int maxd, int S, uint32_t corner)
+{
+    const uint32_t nn = C->node_count;
+    uint32_t end[NLEV];  // end of every level but the last
+#pragma unroll
+    for (int l = 0; l < G4_MAXLEV; l++) end[l] = l < maxd ? C->lvl_start[l + 1] : 0xffffffffu;
+    for (uint32_t q = blockIdx.x * blockDim.x + threadIdx.x; q < nn; q += gridDim.x * blockDim.x) {
+        int level = 0;
+#pragma unroll
+        for (int l = 0; l < G4_MAXLEV; l++) level += q >= end[l] ? 1 : 0;
+        const uint32_t first = bfirst[q], count = bcount[q] - first;  // k_emit left the end there
+        bcount[q] = count;
+        const bool split = (lev[first] >> 8) > level;
+        // the geometric centre of the cube from any particle inside it
+        const uint4 p0 = parts[first];
+        const int sh = S - level;
+        WNode w;
+        uint32_t pc[3] = {p0.x, p0.y, p0.z}, g[3];
+        for (int k = 0; k < 3; k++) {
+            uint64_t rel = (uint64_t)(uint32_t)(pc[k] - corner);
+            g[k] = (uint32_t)((uint64_t)corner + ((rel >> sh) << sh) + (1ull << (sh - 1)));
+        }
+        w.gx = g[0];
+        w.gy = g[1];
+        w.gz = g[2];
+        w.cx = g[0];
+        w.cy = g[1];
+        w.cz = g[2];
+        w.mass = 0.f;
+        for (int k = 0; k < 6; k++) w.q[k] = 0.f;
+        if (split) {
+            w.next = cfirst[q];
+            w.num = cend[q] - w.next;
+            w.meta = (uint32_t)level;
+        } else {
+            w.next = first;
+            w.num = count;
+            w.meta = (uint32_t)level | WN_LEAF;
+            if (count > (uint32_t)B) atomicOr(&C->flags, 1u);
+        }
+        wn[q] = w;
     }
 }
 
@@ -494,27 +494,52 @@ static int sort_keys(g4_ctx *ctx, g4_tree *t)
     return G4_OK;
 }
 
+// nodes from the sorted keys (keys1, parts); box: box of every sorted particle
+// of a forest, or null.  Scratch: keys0 (levels, window maxima), the sort's
+// tables (starts per block), the octupoles' place (children of each node).
+static int launch_nodes(g4_ctx *ctx, g4_tree *t, const uint32_t *box)
+{
+    hipStream_t s = ctx->stream;
+    const int64_t n = t->n, B = t->tp.leaf_max;
+    const int maxd = t->tp.max_depth < 1 ? 1 : (t->tp.max_depth > G4_MAXLEV ? G4_MAXLEV : t->tp.max_depth);
+    uint16_t *lev = reinterpret_cast<uint16_t *>(t->keys0);
+    uint8_t *w[2] = {reinterpret_cast<uint8_t *>(lev + n), reinterpret_cast<uint8_t *>(lev + n) + n};
+    uint32_t *cnt = static_cast<uint32_t *>(t->sort_tmp);
+    uint32_t *cfirst = reinterpret_cast<uint32_t *>(t->q3), *cend = cfirst + t->cap;
+    const uint32_t nblk = (uint32_t)((n + LV_TILE - 1) / LV_TILE);
+    if ((size_t)NLEV * nblk * sizeof(uint32_t) > t->sort_tmp_bytes)
+        return g4_set_err(ctx, G4_ENOMEM, "level tables exceed the sort scratch");
+    const uint8_t *wmax = nullptr;
+    if (B > LV_MAXB) {
+        int cur = 0;
+        int64_t span = 1;
+        k_window<<<grid_for(n), kBlock, 0, s>>>(t->keys1, box, n, B, w[0]);
+        for (; 2 * span <= B + 1; span *= 2, cur ^= 1) k_window_max<<<grid_for(n), kBlock, 0, s>>>(w[cur], n, span, w[cur ^ 1]);
+        k_window_max<<<grid_for(n), kBlock, 0, s>>>(w[cur], n, B + 1 - span, w[cur ^ 1]);
+        wmax = w[cur ^ 1];
+    }
+    k_levels<<<nblk, LV_TILE, 0, s>>>(t->keys1, box, wmax, n, B, maxd, lev, cnt, nblk);
+    k_level_scan<<<NLEV, 1024, 0, s>>>(cnt, nblk, t->ctr);
+    k_emit<<<nblk, LV_TILE, 0, s>>>(lev, n, maxd, cnt, nblk, t->ctr, t->bfirst, t->bcount, t->parent, cfirst, cend, t->cap);
+    // the node count is known on the device only; about n / 3 at small leaves, n / 8 at 32
+    k_records<<<grid_for(n, 2048), kBlock, 0, s>>>(t->ctr, lev, t->parts, t->bfirst, t->bcount, cfirst, cend, t->wn, (int)B,
+                                                  maxd, t->S, t->corner);
+    G4_HIP(ctx, hipGetLastError());
+    return G4_OK;
+}
+
 int g4_launch_build(g4_ctx *ctx, g4_tree *t, const g4_particles *p)
 {
     hipStream_t s = ctx->stream;
     const int64_t n = t->n;
-    const int maxd = t->tp.max_depth < 1 ? 1 : (t->tp.max_depth > G4_MAXLEV ? G4_MAXLEV : t->tp.max_depth);
     k_keys<<<grid_for(n), kBlock, 0, s>>>(p->x, p->y, p->z, p->mass, n, t->S - G4_MAXLEV, t->corner,
                                           t->tp.key_kind, t->keys0, t->perm0, packed_staging(t));
     G4_HIP(ctx, hipGetLastError());
     if (int st = sort_keys(ctx, t)) return st;
     // sorted keys now live in keys1, the permutation in perm1
     k_gather<<<grid_for(n), kBlock, 0, s>>>(packed_staging(t), t->perm1, n, t->parts);
-    k_init<<<1, 64, 0, s>>>(t->ctr, t->bfirst, t->bcount, t->parent, (uint32_t)n);
     G4_HIP(ctx, hipGetLastError());
-    for (int l = 0; l <= maxd; l++) {
-        // a fixed grid; the kernel reads the true size of the level
-        k_split<<<kSplitBlocks, kBlock, 0, s>>>(t->ctr, t->keys1, t->parts, t->bfirst, t->bcount, t->parent, t->wn, l,
-                                                      t->tp.leaf_max, maxd, t->S, t->corner, t->cap);
-    }
-    k_count_nodes<<<1, 64, 0, s>>>(t->ctr);
-    G4_HIP(ctx, hipGetLastError());
-    return G4_OK;
+    return launch_nodes(ctx, t, nullptr);
 }
 
 // ---------------------------------------------------------------- moments
@@ -874,33 +899,11 @@ __global__ void k_gather_keys(const uint4 *__restrict__ pk, const uint32_t *__re
     }
 }
 
-__global__ void k_init_forest(DevCounters *C, uint32_t *bfirst, uint32_t *bcount, uint32_t *parent,
-                              const int64_t *__restrict__ off, int nbox)
-{
-    const int b = blockIdx.x * blockDim.x + threadIdx.x;
-    if (b == 0) {
-        C->node_count = (uint32_t)nbox;
-        C->flags = 0;
-        for (int l = 0; l < G4_MAXLEV + 4; l++) {
-            C->lvl_start[l] = 0;
-            C->lvl_count[l] = 0;
-        }
-        C->lvl_count[0] = (uint32_t)nbox;
-        for (int s = 0; s < 18; s++) C->stat[s] = 0;
-    }
-    if (b < nbox) {
-        bfirst[b] = (uint32_t)off[b];
-        bcount[b] = (uint32_t)(off[b + 1] - off[b]);
-        parent[b] = 0xffffffffu;
-    }
-}
-
 int g4_launch_build_forest(g4_ctx *ctx, g4_tree *t, const g4_particles *p, const int64_t *off_dev, uint32_t *bkey0,
                            uint32_t *bkey1)
 {
     hipStream_t s = ctx->stream;
     const int64_t n = t->n;
-    const int maxd = t->tp.max_depth < 1 ? 1 : (t->tp.max_depth > G4_MAXLEV ? G4_MAXLEV : t->tp.max_depth);
     k_keys<<<grid_for(n), kBlock, 0, s>>>(p->x, p->y, p->z, p->mass, n, t->S - G4_MAXLEV, t->corner,
                                           t->tp.key_kind, t->keys0, t->perm0, packed_staging(t));
     G4_HIP(ctx, hipGetLastError());
@@ -916,12 +919,6 @@ int g4_launch_build_forest(g4_ctx *ctx, g4_tree *t, const g4_particles *p, const
     if (alt) std::swap(t->perm0, t->perm1);
     k_gather_keys<<<grid_for(n), kBlock, 0, s>>>(packed_staging(t), t->perm1, n, t->S - G4_MAXLEV, t->corner,
                                                   t->tp.key_kind, t->parts, t->keys1);
-    k_init_forest<<<(t->nbox + 255) / 256, 256, 0, s>>>(t->ctr, t->bfirst, t->bcount, t->parent, off_dev, t->nbox);
     G4_HIP(ctx, hipGetLastError());
-    for (int l = 0; l <= maxd; l++)
-        k_split<<<kSplitBlocks, kBlock, 0, s>>>(t->ctr, t->keys1, t->parts, t->bfirst, t->bcount, t->parent,
-                                                      t->wn, l, t->tp.leaf_max, maxd, t->S, t->corner, t->cap);
-    k_count_nodes<<<1, 64, 0, s>>>(t->ctr);
-    G4_HIP(ctx, hipGetLastError());
-    return G4_OK;
+    return launch_nodes(ctx, t, alt ? bkey1 : bkey0);
 }

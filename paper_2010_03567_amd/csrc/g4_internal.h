@@ -54,13 +54,13 @@ static_assert(sizeof(WNode) == 64, "WNode must be 64 bytes");
 
 // Device counters at the head of the tree workspace.
 struct DevCounters {
-    uint32_t node_count;      // total nodes (the level sizes summed after the split passes)
+    uint32_t node_count;      // total nodes
     uint32_t item_ctr;        // work-item counter of the persistent walk
     uint32_t flags;           // bit 0: depth-capped leaf above leaf_max; bit 1: node overflow;
                               // bit 2: walk stack overflow; bit 3: FMM leaf-node stack overflow
     uint32_t pad;
     uint32_t lvl_start[G4_MAXLEV + 4];  // first node of each level
-    uint32_t lvl_count[G4_MAXLEV + 4];  // nodes of each level (children allocated by atomics)
+    uint32_t lvl_count[G4_MAXLEV + 4];  // nodes of each level
     unsigned long long stat[18];  // [0..2] walk p2p/p2m/visits, [3..5] seed walk, [6..8] FMM pp/pn/nn,
                                   // [9..15] walk passes, deepest stack, entries, leaves, chunks,
                                   // [16..17] walk pairs used / dropped by a decision for the whole group
