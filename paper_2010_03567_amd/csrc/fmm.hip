@@ -71,6 +71,12 @@ struct FmmArgs {
     unsigned long long *stat;  // pp, pn, nn
 };
 
+__device__ __forceinline__ void fm_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
 // ---------------------------------------------------------------- geometry
 // |d| of an int32 nearest-image offset given as u32 (2^31 for the most negative one)
 __device__ __forceinline__ uint32_t fm_uabs(uint32_t u) { return (int32_t)u < 0 ? 0u - u : u; }
@@ -469,13 +475,13 @@ __device__ __forceinline__ void gfun_f(int kernel, float r2, float asplit, float
     }
 }
 
-// add the field of a source (mass M, Q2, Q3; Q2 = Q3 = null for a particle)
-// seen at r = s_source - s_sink: F0 += M D0 + Q2:D2/2 + Q3.D3/6,
-// F1 += M D1 + Q2:D3/2, F2 += M D2, F3 += M D3.
-__device__ __forceinline__ void add_field_f(float F[20], const float r[3], float g0, float g1, float g2, float g3,
-                                            float M, const float *Q2, const float *Q3)
+// The field of a source (mass M, Q2, Q3; Q2 = Q3 = null for a particle) seen at
+// r = s_source - s_sink: f0 = M D0 + Q2:D2/2 + Q3.D3/6, f1 = M D1 + Q2:D3/2, and
+// D2, D3 (times M the second and third derivatives).
+__device__ __forceinline__ void field_terms(const float r[3], float g0, float g1, float g2, float g3, float M,
+                                            const float *Q2, const float *Q3, float &f0, float f1[3], float D2[6],
+                                            float D3[10])
 {
-    float D2[6], D3[10];
 #pragma unroll
     for (int i = 0; i < 3; i++)
 #pragma unroll
@@ -492,8 +498,9 @@ __device__ __forceinline__ void add_field_f(float F[20], const float r[3], float
                 if (i == k) t += r[j];
                 D3[i3(i, j, k)] = g2 * t + g3 * r[i] * r[j] * r[k];
             }
-    float f0 = M * g0;
-    float f1[3] = {M * g1 * r[0], M * g1 * r[1], M * g1 * r[2]};
+    f0 = M * g0;
+#pragma unroll
+    for (int i = 0; i < 3; i++) f1[i] = M * g1 * r[i];
     if (Q2) {
         const float tr = Q2[0] + Q2[3] + Q2[5];
         const float qr[3] = {Q2[0] * r[0] + Q2[1] * r[1] + Q2[2] * r[2], Q2[1] * r[0] + Q2[3] * r[1] + Q2[4] * r[2],
@@ -515,6 +522,14 @@ __device__ __forceinline__ void add_field_f(float F[20], const float r[3], float
             f0 += (3.f * g2 * (tv[0] * r[0] + tv[1] * r[1] + tv[2] * r[2]) + g3 * c3) * (1.0f / 6.0f);
         }
     }
+}
+
+// add a source's field to an expansion: F0 += f0, F1 += f1, F2 += M D2, F3 += M D3
+__device__ __forceinline__ void add_field_f(float F[20], const float r[3], float g0, float g1, float g2, float g3,
+                                            float M, const float *Q2, const float *Q3)
+{
+    float f0, f1[3], D2[6], D3[10];
+    field_terms(r, g0, g1, g2, g3, M, Q2, Q3, f0, f1, D2, D3);
     F[0] += f0;
     F[1] += f1[0];
     F[2] += f1[1];
@@ -529,12 +544,13 @@ __device__ __forceinline__ void add_field_f(float F[20], const float r[3], float
 // a source gets the same expansion with psi's derivatives D (packed D0..D3 at
 // r = s_source - s_sink) subtracted: F0 -= M D0 + Q2:D2/2 + Q3.D3/6,
 // F1 -= M D1 + Q2:D3/2, F2 -= M D2, F3 -= M D3.
-__device__ __forceinline__ void sub_field_psi(float F[20], const float D[20], float M, const float *Q2,
-                                              const float *Q3)
+__device__ __forceinline__ void psi_terms(const float D[20], float M, const float *Q2, const float *Q3, float &f0,
+                                          float f1[3])
 {
     const float *D1 = D + 1, *D2 = D + 4, *D3 = D + 10;
-    float f0 = M * D[0];
-    float f1[3] = {M * D1[0], M * D1[1], M * D1[2]};
+    f0 = M * D[0];
+#pragma unroll
+    for (int i = 0; i < 3; i++) f1[i] = M * D1[i];
     if (Q2) {
         // symmetric contractions in packed storage (off-diagonal terms twice)
         f0 += 0.5f * (Q2[0] * D2[0] + Q2[3] * D2[3] + Q2[5] * D2[5]) + Q2[1] * D2[1] + Q2[2] * D2[2] +
@@ -559,14 +575,19 @@ __device__ __forceinline__ void sub_field_psi(float F[20], const float D[20], fl
             f0 += c3 * (1.0f / 6.0f);
         }
     }
+}
+
+__device__ __forceinline__ void sub_field_psi(float F[20], const float D[20], float M, const float *Q2,
+                                              const float *Q3)
+{
+    float f0, f1[3];
+    psi_terms(D, M, Q2, Q3, f0, f1);
     F[0] -= f0;
     F[1] -= f1[0];
     F[2] -= f1[1];
     F[3] -= f1[2];
 #pragma unroll
-    for (int a = 0; a < 6; a++) F[4 + a] -= M * D2[a];
-#pragma unroll
-    for (int a = 0; a < 10; a++) F[10 + a] -= M * D3[a];
+    for (int a = 4; a < 20; a++) F[a] -= M * D[a];
 }
 
 // psi's packed D0..D3 at -r from those at r (psi is even: odd orders change sign)
@@ -578,19 +599,32 @@ __device__ __forceinline__ void psi_mirror(float D[20])
     for (int a = 10; a < 20; a++) D[a] = -D[a];
 }
 
-// M2L / P2L: each node sums the fields of its sources
+// M2L / P2L: each node sums the fields of its sources, in list order.  One
+// wavefront per node: 64 sources at a time, a lane computes one source's terms
+// and leaves them in LDS; then lane a < 20 adds coefficient a of all of them in
+// order (F0, F1 a sum, F2, F3 a product with the source's mass), the same chain of
+// FP32 operations as one thread going through the list.  A node has some 300
+// sources, the top ones many more, which one thread per node took one by one:
+// 30 k particles 2.38 -> 0.10 ms.
+#define M2L_ROW 21  // 20 terms and the mass
+
 template <bool EW>
 __global__ __launch_bounds__(256) void k_fmm_m2l(FmmArgs A, const uint32_t *__restrict__ start,
                                                  const uint32_t *__restrict__ end, float *__restrict__ F)
 {
+    __shared__ float terms[4][64 * M2L_ROW], psi[EW ? 4 : 1][EW ? 64 * M2L_ROW : 1];
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     const uint32_t nn = A.ctr->node_count;
-    for (uint32_t q = blockIdx.x * blockDim.x + threadIdx.x; q < nn; q += gridDim.x * blockDim.x) {
-        float f[20];
-#pragma unroll
-        for (int a = 0; a < 20; a++) f[a] = 0.f;
-        const WNode w = A.wn[q];
-        for (uint32_t e = start[q]; e < end[q]; e++) {
-            const uint32_t src = A.nval[e];
+    const uint32_t q = blockIdx.x * 4 + wv;
+    if (q >= nn) return;
+    float *T = terms[wv], *P = psi[EW ? wv : 0];
+    const WNode w = A.wn[q];
+    const uint32_t e1 = end[q];
+    float acc = 0.f;  // coefficient `lane`
+    for (uint32_t e0 = start[q]; e0 < e1; e0 += 64) {
+        const uint32_t cnt = min(64u, e1 - e0);
+        if ((uint32_t)lane < cnt) {
+            const uint32_t src = A.nval[e0 + lane];
             const uint32_t id = ENT_IDX(src);
             float r[3], M;
             const float *Q2 = nullptr, *Q3 = nullptr;
@@ -614,18 +648,42 @@ __global__ __launch_bounds__(256) void k_fmm_m2l(FmmArgs A, const uint32_t *__re
                 Q2 = q2;
                 Q3 = q3;
             }
-            float g0, g1, g2, g3;
+            float g0, g1, g2, g3, f0, f1[3], D2[6], D3[10];
             gfun_f(A.kernel, r[0] * r[0] + r[1] * r[1] + r[2] * r[2], A.asplit, g0, g1, g2, g3);
-            add_field_f(f, r, g0, g1, g2, g3, M, Q2, Q3);
+            field_terms(r, g0, g1, g2, g3, M, Q2, Q3, f0, f1, D2, D3);
+            float *t = T + lane * M2L_ROW;
+            t[0] = f0;
+#pragma unroll
+            for (int a = 0; a < 3; a++) t[1 + a] = f1[a];
+#pragma unroll
+            for (int a = 0; a < 6; a++) t[4 + a] = D2[a];
+#pragma unroll
+            for (int a = 0; a < 10; a++) t[10 + a] = D3[a];
+            t[20] = M;
             if constexpr (EW) {
                 float D[20];
                 ew_d20(A.ew, A.ew_n, A.ew_h, A.ew_hinv, r[0], r[1], r[2], D);
-                sub_field_psi(f, D, M, Q2, Q3);
+                psi_terms(D, M, Q2, Q3, f0, f1);
+                float *u = P + lane * M2L_ROW;
+                u[0] = f0;
+#pragma unroll
+                for (int a = 0; a < 3; a++) u[1 + a] = f1[a];
+#pragma unroll
+                for (int a = 4; a < 20; a++) u[a] = D[a];
             }
         }
-#pragma unroll
-        for (int a = 0; a < 20; a++) F[(size_t)q * 20 + a] = f[a];
+        fm_sync();
+        if (lane < 20) {
+#pragma unroll 4
+            for (uint32_t k = 0; k < cnt; k++) {
+                const float c = lane < 4 ? 1.f : T[k * M2L_ROW + 20];
+                acc = fmaf(c, T[k * M2L_ROW + lane], acc);
+                if constexpr (EW) acc = fmaf(-c, P[k * M2L_ROW + lane], acc);
+            }
+        }
+        fm_sync();
     }
+    if (lane < 20) F[(size_t)q * 20 + lane] = acc;
 }
 
 // L2L for one level: F_child += shift of F_parent by d = s_child - s_parent:
@@ -694,8 +752,10 @@ __global__ void k_fmm_leafmap(const DevCounters *__restrict__ C, const WNode *__
     }
 }
 
-// Per particle: M2P from node sources, P2P from particle or leaf sources,
-// then L2P of the leaf's field expansion: a = G[-F1 + F2.a - F3:aa/2],
+// Per particle: M2P from node sources, P2P from particle or leaf sources (16
+// lanes per particle take its sources in turn, their FP64 sums close in a fixed
+// order; one thread per particle left most of the chip idle: 30 k particles 1.57
+// -> 0.15 ms), then L2P of the leaf's field expansion: a = G[-F1 + F2.a - F3:aa/2],
 // phi = -G[F0 - F1.a + F2:aa/2 - F3:aaa/6], a = x - s_leaf.
 template <int KER, bool POT>
 __global__ __launch_bounds__(256) void k_fmm_particles(FmmArgs A, const uint32_t *__restrict__ start,
@@ -705,11 +765,12 @@ __global__ __launch_bounds__(256) void k_fmm_particles(FmmArgs A, const uint32_t
                                                        int64_t n, double G, double *ax, double *ay, double *az,
                                                        double *pot)
 {
-    const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+    const int64_t i = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) >> 4;
+    const uint32_t sub = threadIdx.x & 15;
     if (i >= n) return;
     const uint4 me = A.parts[i];
     double dx_ = 0, dy_ = 0, dz_ = 0, dp_ = 0;
-    for (uint32_t e = start[i]; e < end[i]; e++) {
+    for (uint32_t e = start[i] + sub; e < end[i]; e += 16) {
         const uint32_t src = A.pval[e];
         const uint32_t id = ENT_IDX(src);
         float fx = 0.f, fy = 0.f, fz = 0.f, fp = 0.f;
@@ -769,6 +830,14 @@ __global__ __launch_bounds__(256) void k_fmm_particles(FmmArgs A, const uint32_t
         dz_ += fz;
         if (POT) dp_ += fp;
     }
+#pragma unroll
+    for (int off = 8; off > 0; off >>= 1) {
+        dx_ += __shfl_xor(dx_, off);
+        dy_ += __shfl_xor(dy_, off);
+        dz_ += __shfl_xor(dz_, off);
+        if (POT) dp_ += __shfl_xor(dp_, off);
+    }
+    if (sub) return;
     // L2P
     const uint32_t L = leafid[i];
     const WNode wl = A.wn[L];
@@ -871,11 +940,6 @@ __device__ __forceinline__ uint64_t fm_ballot(bool c) { return __builtin_amdgcn_
 __device__ __forceinline__ uint32_t fm_below(uint64_t m)
 {
     return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
-}
-__device__ __forceinline__ void fm_sync()
-{
-    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-    __builtin_amdgcn_wave_barrier();
 }
 
 // Two nodes: 0 dropped (beyond r_cut), 1 interact, 2 open.  Same arithmetic
@@ -2112,13 +2176,13 @@ int g4_launch_fmm(g4_ctx *ctx, g4_tree *t, const g4_fmm_params *fp, double facto
     A.nval = nv2;
     A.pval = pv2;
     float *F = (float *)(b + L.F);
-    if (fp->kernel == 2) k_fmm_m2l<true><<<(unsigned)((nn_host + 255) / 256), 256, 0, s>>>(A, nstart, nend, F);
-    else k_fmm_m2l<false><<<(unsigned)((nn_host + 255) / 256), 256, 0, s>>>(A, nstart, nend, F);
+    if (fp->kernel == 2) k_fmm_m2l<true><<<(unsigned)((nn_host + 3) / 4), 256, 0, s>>>(A, nstart, nend, F);
+    else k_fmm_m2l<false><<<(unsigned)((nn_host + 3) / 4), 256, 0, s>>>(A, nstart, nend, F);
     const int maxd = t->tp.max_depth;
     for (int l = 1; l <= maxd; l++) k_fmm_l2l<<<1024, 256, 0, s>>>(A, l, F);
     uint32_t *leafid = (uint32_t *)(b + L.leafid);
     k_fmm_leafmap<<<(unsigned)((nn_host + 255) / 256), 256, 0, s>>>(t->ctr, t->wn, leafid);
-    const unsigned pb = (unsigned)((t->n + 255) / 256);
+    const unsigned pb = (unsigned)((t->n + 15) / 16);
     if (fp->kernel == 2) {
         if (pot) k_fmm_particles<2, true><<<pb, 256, 0, s>>>(A, pstart, pend, F, leafid, t->perm1, t->n, fp->G, ax, ay, az, pot);
         else k_fmm_particles<2, false><<<pb, 256, 0, s>>>(A, pstart, pend, F, leafid, t->perm1, t->n, fp->G, ax, ay, az, pot);
