@@ -38,6 +38,16 @@
 #define ENT_IDX(e) ((e) & 0x3fffffffu)
 #define ENT_TYPE(e) ((e) & 0xc0000000u)
 
+// Counter words of a call: [2..4] lists and overflow, three frontier sizes that
+// take turns as in, out and cleared (so that no launch rotates them between
+// passes), and the tree's node count and level sizes, so that one copy brings
+// the host all it asks for.
+#define FMM_FRONT 8
+#define FMM_NODES 12
+#define FMM_LEVELS 16
+#define FMM_WORDS (FMM_LEVELS + G4_MAXLEV + 1)
+#define FMM_CNT_BYTES 256
+
 struct FmmArgs {
     const WNode *wn;
     const uint32_t *bfirst;  // first particle of each node
@@ -59,7 +69,8 @@ struct FmmArgs {
     // frontier and entry lists
     const uint2 *fin;
     uint2 *fout;
-    uint32_t *cnt;   // [0] in-count (read), [1] out-count, [2] node entries, [3] particle entries, [4] overflow
+    uint32_t *cnt;   // [2] node entries, [3] particle entries, [4] overflow (FMM_* below)
+    uint32_t *cin, *cout, *cnext;  // this pass's and the next one's frontier sizes; the one after, cleared
     uint32_t cap_pairs;
     // entries: key = target << 32 | order key of the source, value = source (type bits | index)
     uint64_t *nkey;
@@ -318,9 +329,10 @@ __global__ __launch_bounds__(256) void k_fmm_traverse(FmmArgs A)
     // block, since every thread of the block must reach the barriers of the appends)
     __shared__ uint32_t s_over;
     if (threadIdx.x == 0) s_over = A.cnt[4];
+    if (blockIdx.x == 0 && threadIdx.x == 0) *A.cnext = 0;
     __syncthreads();
     if (s_over) return;
-    const uint32_t nin = min(A.cnt[0], A.cap_pairs);
+    const uint32_t nin = min(*A.cin, A.cap_pairs);
     // interaction counters: particle pairs, particle-node, node-node (summed over the loop,
     // one atomic per wavefront at the end)
     unsigned long long c_pp = 0, c_pn = 0, c_nn = 0;
@@ -333,7 +345,7 @@ __global__ __launch_bounds__(256) void k_fmm_traverse(FmmArgs A)
             const uint2 pr = A.fin[t];
             X = classify(A, pr.x, pr.y);
         }
-        const uint3 off3 = block_append3(&A.cnt[1], &A.cnt[2], &A.cnt[3], X.n_pairs, X.n_node, X.n_part);
+        const uint3 off3 = block_append3(A.cout, &A.cnt[2], &A.cnt[3], X.n_pairs, X.n_node, X.n_part);
         const uint32_t op = off3.x, on = off3.y, ok = off3.z;
         if (X.kind == ACT_PP) c_pp += 1;
         if (X.kind == ACT_OPEN_PP) c_pp += (unsigned long long)X.na * X.nb;
@@ -402,23 +414,16 @@ __global__ __launch_bounds__(256) void k_fmm_traverse(FmmArgs A)
     }
 }
 
-// counts: in <- out, clear out (a single thread between passes)
-__global__ void k_fmm_rotate(uint32_t *cnt)
-{
-    if (threadIdx.x == 0 && blockIdx.x == 0) {
-        cnt[0] = cnt[1];
-        cnt[1] = 0;
-    }
-}
-
 // the walk starts from the self-pair of every root (one root per box of a forest)
-__global__ void k_fmm_init(uint32_t *cnt, uint2 *f0, unsigned long long *stat, int nroot)
+__global__ void k_fmm_init(uint32_t *cnt, uint2 *f0, unsigned long long *stat, const DevCounters *__restrict__ C, int nroot)
 {
     const int b = blockIdx.x * blockDim.x + threadIdx.x;
     if (b < nroot) f0[b] = make_uint2((uint32_t)b, (uint32_t)b);
     if (b == 0) {
-        cnt[0] = (uint32_t)nroot;
-        for (int k = 1; k < 8; k++) cnt[k] = 0;
+        for (int k = 0; k < FMM_LEVELS; k++) cnt[k] = 0;
+        cnt[FMM_FRONT] = (uint32_t)nroot;
+        cnt[FMM_NODES] = C->node_count;
+        for (int l = 0; l <= G4_MAXLEV; l++) cnt[FMM_LEVELS + l] = C->lvl_count[l];
         stat[0] = stat[1] = stat[2] = 0;
     }
 }
@@ -922,7 +927,8 @@ struct FastArgs {
     float ew_h, ew_hinv;
     const uint2 *fin;
     uint2 *fout;
-    uint32_t *cnt;  // [0] frontier in, [1] frontier out, [2] leaf pairs, [3] leaf-node pairs, [4] overflow
+    uint32_t *cnt;  // [2] leaf pairs, [3] leaf-node pairs, [4] overflow (FMM_* below)
+    uint32_t *cin, *cout, *cnext;  // as in FmmArgs
     uint32_t cap_pairs;
     uint2 *ll;      // opened (leaf, leaf) pairs
     uint2 *ln;      // opened (leaf, internal node) pairs
@@ -964,11 +970,15 @@ __device__ __forceinline__ int fm_classify(const FastArgs &A, const WNode &a, co
 
 // the walk starts from the self pair of every internal root (a root leaf only
 // has its own particle pairs, which phase 2 does for every leaf)
-__global__ void k_fast_init(FastArgs A, int nroot)
+__global__ void k_fast_init(FastArgs A, const DevCounters *__restrict__ C, int nroot)
 {
     const int b = blockIdx.x * blockDim.x + threadIdx.x;
+    if (b == 0) {
+        A.cnt[FMM_NODES] = C->node_count;
+        for (int l = 0; l <= G4_MAXLEV; l++) A.cnt[FMM_LEVELS + l] = C->lvl_count[l];
+    }
     if (b >= nroot || (A.wn[b].meta & WN_LEAF)) return;
-    const uint32_t o = atomicAdd(&A.cnt[0], 1u);
+    const uint32_t o = atomicAdd(&A.cnt[FMM_FRONT], 1u);
     if (o < A.cap_pairs) A.fout[o] = make_uint2((uint32_t)b, (uint32_t)b);
     else atomicOr(&A.cnt[4], 1u);
 }
@@ -1049,8 +1059,9 @@ __global__ __launch_bounds__(256) void k_fast_open(FastArgs A)
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     float(*FL)[16][20] = Floc[wv];
     for (int v = lane; v < FT_NC * 320; v += 64) (&FL[0][0][0])[v] = 0.f;
+    if (blockIdx.x == 0 && threadIdx.x == 0) *A.cnext = 0;
     if (A.cnt[4]) return;  // a list overflowed: the host retries with more room
-    const uint32_t nin = min(A.cnt[0], A.cap_pairs);
+    const uint32_t nin = min(*A.cin, A.cap_pairs);
     uint32_t c_nn = 0;
     Stage<128> sf{sbf[wv], 0u}, sn{sbn[wv], 0u};
     Stage<256> sl{sbl[wv], 0u};
@@ -1228,11 +1239,11 @@ __global__ __launch_bounds__(256) void k_fast_open(FastArgs A)
         st_push(sf, (act == 3 && !l1) || (act == 2 && !l1 && !l2), pij);
         st_push(sl, act == 2 && l1 && l2, pij);
         st_push(sn, act == 2 && (l1 != l2), l1 ? pij : make_uint2(cb + j, ca + i));
-        st_flush(sf, false, A.fout, &A.cnt[1], A.cap_pairs, &A.cnt[4]);
+        st_flush(sf, false, A.fout, A.cout, A.cap_pairs, &A.cnt[4]);
         st_flush(sl, false, A.ll, &A.cnt[2], A.cap_ll, &A.cnt[4]);
         st_flush(sn, false, A.ln, &A.cnt[3], A.cap_ln, &A.cnt[4]);
     }
-    st_flush(sf, true, A.fout, &A.cnt[1], A.cap_pairs, &A.cnt[4]);
+    st_flush(sf, true, A.fout, A.cout, A.cap_pairs, &A.cnt[4]);
     st_flush(sl, true, A.ll, &A.cnt[2], A.cap_ll, &A.cnt[4]);
     st_flush(sn, true, A.ln, &A.cnt[3], A.cap_ln, &A.cnt[4]);
     if (lane == 0 && c_nn) atomicAdd(&A.stat[2], (unsigned long long)c_nn);
@@ -1825,7 +1836,7 @@ static int fmm_layout(int64_t n, int64_t cap_nodes, double factor, FmmLayout *L)
         off += (b + 255) & ~(size_t)255;
         return o;
     };
-    L->cnt = take(64);
+    L->cnt = take(FMM_CNT_BYTES);
     L->f0 = take((size_t)L->cap_pairs * 8);
     L->f1 = take((size_t)L->cap_pairs * 8);
     L->nkey = take((size_t)L->cap_node * 8);
@@ -1866,7 +1877,7 @@ static void fast_layout(int64_t n, int64_t cap_nodes, double factor, FastLayout 
         off += (b + 255) & ~(size_t)255;
         return o;
     };
-    L->cnt = take(64);
+    L->cnt = take(FMM_CNT_BYTES);
     L->f0 = take((size_t)L->cap_pairs * 8);
     L->f1 = take((size_t)L->cap_pairs * 8);
     L->ll = take((size_t)L->cap_ll * 8);
@@ -1897,6 +1908,9 @@ int g4_fmm_layout_bytes(const g4_tree *t, const g4_fmm_params *fp, double factor
     return G4_OK;
 }
 
+// blocks of the downward shift of a level of `nodes` nodes (read back with the list sizes)
+static inline unsigned l2l_grid(uint32_t nodes) { return std::min(1024u, (nodes + 255) / 256); }
+
 // Relative criterion: the caller's |a| in sorted order (the tree's seed
 // buffer) and each node's minimum, levels from the deepest up.
 static int fmm_seed_minima(g4_ctx *ctx, g4_tree *t, const g4_fmm_params *fp, float *amin)
@@ -1917,6 +1931,15 @@ static void launch_fast_particles(const FastArgs &A, uint32_t nnodes, uint32_t n
 {
     k_fast_pp<KER, POT><<<(unsigned)std::min<uint64_t>(4096, ((uint64_t)nnodes + 3) / 4), 256, 0, s>>>(A, nnodes);
     if (nln) k_fast_ln<KER, POT><<<(unsigned)std::min<uint64_t>(4096, ((uint64_t)nln + 3) / 4), 256, 0, s>>>(A, nln);
+}
+
+// the frontier counters of one pass
+template <typename Args>
+static void fmm_turn(Args &A, int pass)
+{
+    A.cin = A.cnt + FMM_FRONT + pass % 3;
+    A.cout = A.cnt + FMM_FRONT + (pass + 1) % 3;
+    A.cnext = A.cnt + FMM_FRONT + (pass + 2) % 3;
 }
 
 static int fmm_fast(g4_ctx *ctx, g4_tree *t, const g4_fmm_params *fp, double factor, void *ws, size_t ws_bytes,
@@ -1966,21 +1989,22 @@ static int fmm_fast(g4_ctx *ctx, g4_tree *t, const g4_fmm_params *fp, double fac
     A.flags = &t->ctr->flags;
     uint2 *fr[2] = {(uint2 *)(b + L.f0), (uint2 *)(b + L.f1)};
     if ((uint64_t)t->nbox > L.cap_pairs) return g4_set_err(ctx, G4_ENOMEM, "fmm frontier smaller than the root count");
-    if (int zst = g4_launch_zero(ctx, A.cnt, 64)) return zst;
+    if (int zst = g4_launch_zero(ctx, A.cnt, FMM_CNT_BYTES)) return zst;
     if (int zst = g4_launch_zero(ctx, A.stat, 3 * sizeof(unsigned long long))) return zst;
     if (int zst = g4_launch_zero(ctx, A.F, (size_t)t->cap * 20 * 4)) return zst;
     A.fin = fr[1];
     A.fout = fr[0];
-    k_fast_init<<<(t->nbox + 255) / 256, 256, 0, s>>>(A, t->nbox);
+    k_fast_init<<<(t->nbox + 255) / 256, 256, 0, s>>>(A, t->ctr, t->nbox);
     G4_HIP(ctx, hipGetLastError());
     // 1. node-level dual walk: one pass per level until the frontier is empty (1024 blocks of
     //    4 wavefronts grid-stride over a pass's pairs: measured faster than 512, 2048 or 4096)
     const bool P = pot != nullptr;
-    int cur = 0;
-    uint32_t h4[8];
-    for (int pass = 0; pass < 64; pass++) {
-        A.fin = fr[cur];
-        A.fout = fr[cur ^ 1];
+    uint32_t hc[FMM_WORDS];
+    bool done = false;
+    for (int pass = 0; pass < 64 && !done; pass++) {
+        A.fin = fr[pass & 1];
+        A.fout = fr[(pass & 1) ^ 1];
+        fmm_turn(A, pass);
         if (fp->kernel == 2) {
             if (P) k_fast_open<true, true><<<1024, 256, 0, s>>>(A);
             else k_fast_open<false, true><<<1024, 256, 0, s>>>(A);
@@ -1988,24 +2012,18 @@ static int fmm_fast(g4_ctx *ctx, g4_tree *t, const g4_fmm_params *fp, double fac
             if (P) k_fast_open<true, false><<<1024, 256, 0, s>>>(A);
             else k_fast_open<false, false><<<1024, 256, 0, s>>>(A);
         }
-        k_fmm_rotate<<<1, 64, 0, s>>>(A.cnt);
-        cur ^= 1;
         if ((pass & 3) == 3) {
-            G4_HIP(ctx, hipMemcpyAsync(h4, A.cnt, sizeof(h4), hipMemcpyDeviceToHost, s));
+            G4_HIP(ctx, hipGetLastError());
+            G4_HIP(ctx, hipMemcpyAsync(hc, A.cnt, sizeof(hc), hipMemcpyDeviceToHost, s));
             G4_HIP(ctx, hipStreamSynchronize(s));
-            if (h4[4]) return g4_set_err(ctx, G4_ENOMEM, "fmm lists exceed the workspace");
-            if (h4[0] == 0) break;
+            if (hc[4]) return g4_set_err(ctx, G4_ENOMEM, "fmm lists exceed the workspace");
+            done = hc[FMM_FRONT + (pass + 1) % 3] == 0;
         }
     }
-    G4_HIP(ctx, hipGetLastError());
-    uint32_t nnodes = 0;
-    G4_HIP(ctx, hipMemcpyAsync(h4, A.cnt, sizeof(h4), hipMemcpyDeviceToHost, s));
-    G4_HIP(ctx, hipMemcpyAsync(&nnodes, &t->ctr->node_count, 4, hipMemcpyDeviceToHost, s));
-    G4_HIP(ctx, hipStreamSynchronize(s));
-    if (h4[4]) return g4_set_err(ctx, G4_ENOMEM, "fmm lists exceed the workspace");
-    if (h4[0] != 0) return g4_set_err(ctx, G4_EHIP, "fmm dual walk did not terminate");
+    if (!done) return g4_set_err(ctx, G4_EHIP, "fmm dual walk did not terminate");
+    const uint32_t nnodes = hc[FMM_NODES], *levels = hc + FMM_LEVELS;
     if (nnodes < 1 || (int64_t)nnodes > t->cap) return g4_set_err(ctx, G4_EHIP, "bad node count");
-    const uint32_t nll = h4[2], nln = h4[3];
+    const uint32_t nll = hc[2], nln = hc[3];
     // 2. partner lists of the leaf pairs (counting sort by leaf), then all particle pairs per leaf
     uint32_t *cursor = (uint32_t *)(b + L.cursor), *bsum = (uint32_t *)(b + L.bsum);
     if (int zst = g4_launch_zero(ctx, A.pstart, (size_t)(nnodes + 1) * 4)) return zst;
@@ -2033,7 +2051,7 @@ static int fmm_fast(g4_ctx *ctx, g4_tree *t, const g4_fmm_params *fp, double fac
     D.parent = t->parent;
     D.unit = A.unit;
     const int maxd = t->tp.max_depth;
-    for (int l = 1; l <= maxd; l++) k_fmm_l2l<<<1024, 256, 0, s>>>(D, l, A.F);
+    for (int l = 1; l <= maxd && levels[l]; l++) k_fmm_l2l<<<l2l_grid(levels[l]), 256, 0, s>>>(D, l, A.F);
     uint32_t *leafid = (uint32_t *)(b + L.leafid);
     k_fmm_leafmap<<<(unsigned)std::min<uint32_t>(65535, (nnodes + 255) / 256), 256, 0, s>>>(t->ctr, t->wn, leafid);
     const unsigned pb = (unsigned)((t->n + 255) / 256);
@@ -2041,15 +2059,15 @@ static int fmm_fast(g4_ctx *ctx, g4_tree *t, const g4_fmm_params *fp, double fac
     else k_fast_finish<false><<<pb, 256, 0, s>>>(A, leafid, t->perm1, t->n, fp->G, ax, ay, az, pot);
     G4_HIP(ctx, hipGetLastError());
     if (stats) {
-        DevCounters hc;
-        G4_HIP(ctx, hipMemcpyAsync(&hc, t->ctr, sizeof(hc), hipMemcpyDeviceToHost, s));
+        DevCounters dc;
+        G4_HIP(ctx, hipMemcpyAsync(&dc, t->ctr, sizeof(dc), hipMemcpyDeviceToHost, s));
         G4_HIP(ctx, hipStreamSynchronize(s));
         std::memset(stats, 0, sizeof(*stats));
-        stats->n_pp = hc.stat[6];
-        stats->n_pn = hc.stat[7];
-        stats->n_nn = hc.stat[8];
-        stats->n_nodes = hc.node_count;
-        stats->flags = hc.flags;
+        stats->n_pp = dc.stat[6];
+        stats->n_pn = dc.stat[7];
+        stats->n_nn = dc.stat[8];
+        stats->n_nodes = dc.node_count;
+        stats->flags = dc.flags;
     }
     return G4_OK;
 }
@@ -2109,38 +2127,27 @@ int g4_launch_fmm(g4_ctx *ctx, g4_tree *t, const g4_fmm_params *fp, double facto
     A.stat = t->ctr->stat + 6;
     uint2 *fr[2] = {(uint2 *)(b + L.f0), (uint2 *)(b + L.f1)};
     if ((uint64_t)t->nbox > L.cap_pairs) return g4_set_err(ctx, G4_ENOMEM, "fmm frontier smaller than the root count");
-    k_fmm_init<<<(t->nbox + 255) / 256, 256, 0, s>>>(A.cnt, fr[0], A.stat, t->nbox);
+    k_fmm_init<<<(t->nbox + 255) / 256, 256, 0, s>>>(A.cnt, fr[0], A.stat, t->ctr, t->nbox);
     G4_HIP(ctx, hipGetLastError());
     // dual walk: passes until the frontier is empty (checked every 8 passes)
-    int cur = 0;
-    for (int pass = 0; pass < 512; pass++) {
-        A.fin = fr[cur];
-        A.fout = fr[cur ^ 1];
+    uint32_t hc[FMM_WORDS];
+    bool done = false;
+    for (int pass = 0; pass < 512 && !done; pass++) {
+        A.fin = fr[pass & 1];
+        A.fout = fr[(pass & 1) ^ 1];
+        fmm_turn(A, pass);
         k_fmm_traverse<<<2048, 256, 0, s>>>(A);
-        k_fmm_rotate<<<1, 64, 0, s>>>(A.cnt);
-        cur ^= 1;
         if ((pass & 7) == 7) {
-            uint32_t h4[8];
-            G4_HIP(ctx, hipMemcpyAsync(h4, A.cnt, sizeof(h4), hipMemcpyDeviceToHost, s));
+            G4_HIP(ctx, hipGetLastError());
+            G4_HIP(ctx, hipMemcpyAsync(hc, A.cnt, sizeof(hc), hipMemcpyDeviceToHost, s));
             G4_HIP(ctx, hipStreamSynchronize(s));
-            if (h4[4]) return g4_set_err(ctx, G4_ENOMEM, "fmm interaction lists exceed the workspace");
-            if (h4[0] == 0) break;
+            if (hc[4]) return g4_set_err(ctx, G4_ENOMEM, "fmm interaction lists exceed the workspace");
+            done = hc[FMM_FRONT + (pass + 1) % 3] == 0;
         }
     }
-    G4_HIP(ctx, hipGetLastError());
-    uint32_t h4[8];
-    G4_HIP(ctx, hipMemcpyAsync(h4, A.cnt, sizeof(h4), hipMemcpyDeviceToHost, s));
-    G4_HIP(ctx, hipStreamSynchronize(s));
-    if (h4[4]) return g4_set_err(ctx, G4_ENOMEM, "fmm interaction lists exceed the workspace");
-    if (h4[0] != 0) return g4_set_err(ctx, G4_EHIP, "fmm dual walk did not terminate");
-    const uint32_t n_node = h4[2], n_part = h4[3];
-    int64_t nn_host = 0;
-    {
-        DevCounters hc;
-        G4_HIP(ctx, hipMemcpyAsync(&hc, t->ctr, sizeof(hc), hipMemcpyDeviceToHost, s));
-        G4_HIP(ctx, hipStreamSynchronize(s));
-        nn_host = hc.node_count;
-    }
+    if (!done) return g4_set_err(ctx, G4_EHIP, "fmm dual walk did not terminate");
+    const uint32_t n_node = hc[2], n_part = hc[3], *levels = hc + FMM_LEVELS;
+    const int64_t nn_host = hc[FMM_NODES];
     // sort the entries by (target, source): each target's sum then runs in source order,
     // independent of the order in which the walk appended its entries
     uint64_t *nk2 = (uint64_t *)(b + L.nkey2), *pk2 = (uint64_t *)(b + L.pkey2);
@@ -2179,7 +2186,7 @@ int g4_launch_fmm(g4_ctx *ctx, g4_tree *t, const g4_fmm_params *fp, double facto
     if (fp->kernel == 2) k_fmm_m2l<true><<<(unsigned)((nn_host + 3) / 4), 256, 0, s>>>(A, nstart, nend, F);
     else k_fmm_m2l<false><<<(unsigned)((nn_host + 3) / 4), 256, 0, s>>>(A, nstart, nend, F);
     const int maxd = t->tp.max_depth;
-    for (int l = 1; l <= maxd; l++) k_fmm_l2l<<<1024, 256, 0, s>>>(A, l, F);
+    for (int l = 1; l <= maxd && levels[l]; l++) k_fmm_l2l<<<l2l_grid(levels[l]), 256, 0, s>>>(A, l, F);
     uint32_t *leafid = (uint32_t *)(b + L.leafid);
     k_fmm_leafmap<<<(unsigned)((nn_host + 255) / 256), 256, 0, s>>>(t->ctr, t->wn, leafid);
     const unsigned pb = (unsigned)((t->n + 15) / 16);
@@ -2195,15 +2202,15 @@ int g4_launch_fmm(g4_ctx *ctx, g4_tree *t, const g4_fmm_params *fp, double facto
     }
     G4_HIP(ctx, hipGetLastError());
     if (stats) {
-        DevCounters hc;
-        G4_HIP(ctx, hipMemcpyAsync(&hc, t->ctr, sizeof(hc), hipMemcpyDeviceToHost, s));
+        DevCounters dc;
+        G4_HIP(ctx, hipMemcpyAsync(&dc, t->ctr, sizeof(dc), hipMemcpyDeviceToHost, s));
         G4_HIP(ctx, hipStreamSynchronize(s));
         std::memset(stats, 0, sizeof(*stats));
-        stats->n_pp = hc.stat[6];
-        stats->n_pn = hc.stat[7];
-        stats->n_nn = hc.stat[8];
-        stats->n_nodes = hc.node_count;
-        stats->flags = hc.flags;
+        stats->n_pp = dc.stat[6];
+        stats->n_pn = dc.stat[7];
+        stats->n_nn = dc.stat[8];
+        stats->n_nodes = dc.node_count;
+        stats->flags = dc.flags;
     }
     return G4_OK;
 }
