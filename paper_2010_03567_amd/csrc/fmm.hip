@@ -904,8 +904,6 @@ __global__ __launch_bounds__(256) void k_fmm_particles(FmmArgs A, const uint32_t
 //  4. downward shift (the kernel above) and evaluation at the particles.
 // Summation order follows the scheduling of the atomics, so results agree
 // with the list-based path to round-off but are not bitwise reproducible.
-#define FT_STK 32  // traversal stack of a leaf-node pair: one sibling entry per level
-#define FT_SB 16   // source block of the particle pairs with an opened leaf
 #define FP_SRC 512 // partner particles listed in LDS at a time by the leaf-pair kernel
 #define FT_NC 2     // copies of the daughters' field sums in the node-pair passes
 
@@ -1485,284 +1483,333 @@ __device__ __forceinline__ void fm_deposit(const FastArgs &A, uint32_t j, float 
     if (POT) atomicAdd(a + 3, (double)fp);
 }
 
-// sums of the 20 values over each aligned 16-lane group (a DPP row), in the group's first
-// lane; the other lanes end with partial sums.  Row shifts with the adds, no LDS traffic;
-// every lane of the wavefront must be active.  `span` (wavefront-uniform: 4, 8 or 16) bounds
-// the lanes of every group that may hold nonzero values: the shifts that would only add
-// zeros are skipped, which leaves every sum bitwise unchanged.
-__device__ __forceinline__ void fm_gsum20(float v[20], uint32_t span)
+// Phase 3: leaf-node pairs, four per wavefront at a time (most hold some ten
+// nodes below the internal one, too few to fill a wavefront for one pair).  Sixteen
+// of a leaf's particles (targets) walk the internal node's subtree together; an
+// entry of the wavefront's stack is a set of sibling nodes with the pair and the
+// mask of its targets that must look at them.  A step takes entries from the top until their (node, target)
+// slots fill the wavefront (leaves hold four particles on average at leaf 16, and
+// masks thin out on the way down, so a single node would leave most lanes idle):
+// the nodes are listed in LDS and every node gets `kp` consecutive lanes, a power
+// of two that holds the largest mask of the step.  Each slot takes the
+// particle-node decision; a slot that interacts computes both sides, the target's
+// force (LDS adds) and the particle's field on the node (summed over the node's
+// lanes by row shifts, then one contiguous atomic per coefficient).  Opened
+// internal nodes become entries, opened leaves go to a second stack whose
+// particles are paired with their targets in the same slots, when they fill the
+// wavefront or nothing else is left.
+// Bound by instruction issue (about 400 a step), with the chain of steps of the
+// longest pair at small sizes.  Groups of 16 lanes that each walked one node at a
+// time had 28 % of their lanes busy: 2^21 particles, leaf 16, 7.1 -> 5.7 ms; 32 k
+// 0.39 -> 0.23 ms.  Of the 5.7 the field atomics take 1.0, the target adds 0.5
+// (2 or 4 copies of them, or five wavefronts per SIMD instead of four: no gain).
+#define FL_TGT 16    // targets of a pair
+#define FL_PAIRS 4   // pairs a wavefront walks at a time
+#define FL_CAP 232   // node entries: FL_DEEP + 64 pushed by one step + 140 of a walk by single entries
+#define FL_DEEP 24   // beyond this depth a step takes one entry, which bounds the stack (7 per level)
+#define FL_LCAP 128  // opened leaves: fewer than 64 pairs left pending, 64 pushed by a step
+#define FL_TOP 8     // entries a step looks at
+#define FL_RED 16    // nodes whose field sums are staged at a time
+
+struct FlStack {
+    uint32_t *first, *count, *mask;  // LDS
+    uint32_t cap;
+    uint32_t n;                      // entries (uniform)
+};
+
+struct __attribute__((aligned(16))) LnLds {
+    uint4 tgt[FL_PAIRS * FL_TGT];      // grid position, mass bits
+    float tacc[FL_PAIRS * FL_TGT][4];  // their sums
+    uint32_t tbase[FL_PAIRS];          // first target particle of each pair
+    uint4 ch[64];  // a step's nodes (or source particles): index, targets | pair << 8, their numbers (4 bits each)
+    float red[FL_RED][20];
+    uint32_t nfirst[FL_CAP], ncount[FL_CAP], nmask[FL_CAP];
+    uint32_t lfirst[FL_LCAP], lcount[FL_LCAP], lmask[FL_LCAP];
+};
+
+// Take entries (at most `most`) from the stack until their slots fill the wavefront:
+// the members are listed in ch, `nc` of them with 2^sh lanes each.  What does not
+// fit of an entry stays on the stack.
+__device__ __forceinline__ void fl_take(FlStack &S, uint32_t most, uint4 *ch, int lane, uint32_t &nc, uint32_t &sh)
 {
-#pragma unroll
-    for (int q = 0; q < 20; q++) {
-        v[q] += __uint_as_float(fm_from_next<1>(__float_as_uint(v[q])));
-        v[q] += __uint_as_float(fm_from_next<2>(__float_as_uint(v[q])));
+    const uint32_t ne = min(S.n, most);
+    uint32_t ef = 0, ec = 0, em = 0;
+    if ((uint32_t)lane < ne) {
+        const uint32_t q = S.n - 1 - (uint32_t)lane;
+        ef = S.first[q];
+        ec = S.count[q];
+        em = S.mask[q];
     }
-    if (span > 4) {
-#pragma unroll
-        for (int q = 0; q < 20; q++) v[q] += __uint_as_float(fm_from_next<4>(__float_as_uint(v[q])));
+    const uint32_t ek = (uint32_t)__builtin_popcount(em & 0xffffu), es = ek > 1 ? 32u - (uint32_t)__builtin_clz(ek - 1) : 0u;
+    nc = sh = 0;
+    uint32_t idx = 0, msk = 0, used = 0;
+    for (uint32_t i = 0; i < ne; i++) {
+        const uint32_t first = (uint32_t)__builtin_amdgcn_readlane((int)ef, (int)i),
+                       count = (uint32_t)__builtin_amdgcn_readlane((int)ec, (int)i),
+                       mask = (uint32_t)__builtin_amdgcn_readlane((int)em, (int)i),
+                       s = max(sh, (uint32_t)__builtin_amdgcn_readlane((int)es, (int)i));
+        const uint32_t room = 64u >> s;
+        if (nc >= room) break;
+        const uint32_t take = min(count, room - nc);
+        if ((uint32_t)lane - nc < take) {
+            idx = first + (uint32_t)lane - nc;
+            msk = mask;
+        }
+        nc += take;
+        sh = s;
+        if (take < count) {
+            if (lane == 0) {
+                S.first[S.n - 1 - i] = first + take;
+                S.count[S.n - 1 - i] = count - take;
+            }
+            break;
+        }
+        used++;
     }
-    if (span > 8) {
+    S.n -= used;
+    if ((uint32_t)lane < nc) {
+        uint64_t list = 0;
+        uint32_t k = 0;
+        for (uint32_t m = msk & 0xffffu; m; m &= m - 1, k++) list |= (uint64_t)__builtin_ctz(m) << (4 * k);
+        ch[lane] = make_uint4(idx, k | (msk >> 16) << 8, (uint32_t)list, (uint32_t)(list >> 32));
+    }
+    fm_sync();
+}
+
+// Push one entry per node with an asking target (want: this lane's target asks;
+// all lanes of a node have the same first and count).
+__device__ __forceinline__ void fl_push(FlStack &S, bool want, uint32_t t, uint32_t first, uint32_t count, uint32_t sh,
+                                        int lane, uint32_t *flags)
+{
+    const uint64_t m = fm_ballot(want);
+    if (!m) return;
+    const uint32_t kp = 1u << sh;
+    const uint64_t seg = m >> (lane & ~(int)(kp - 1)) & ((1ull << kp) - 1ull);  // kp <= 16
+    const bool head = (lane & (kp - 1)) == 0 && seg;
+    const uint64_t heads = fm_ballot(head);
+    if (S.n + (uint32_t)__builtin_popcountll(heads) > S.cap) {
+        // beyond the bounds above: never expected, but never silent
+        if (lane == 0) atomicOr(flags, G4_FLAG_FMM_STACK);
+        return;
+    }
+    // the entry of this lane's node: heads up to the node's first lane
+    const uint32_t q = S.n + (uint32_t)__builtin_popcountll(heads & ((1ull << (lane & ~(int)(kp - 1))) - 1ull));
+    if (head) {
+        S.first[q] = first;
+        S.count[q] = count;
+        S.mask[q] = (t / FL_TGT) << 16;
+    }
+    fm_sync();
+    if (want) atomicOr(&S.mask[q], 1u << (t % FL_TGT));
+    S.n += (uint32_t)__builtin_popcountll(heads);
+    fm_sync();
+}
+
+// sums over the 2^sh lanes of each node, in its first lane (row shifts: 2^sh <= 16; all lanes active)
+template <int N>
+__device__ __forceinline__ void fl_sum(float v[N], uint32_t sh)
+{
+    if (sh > 0) {
 #pragma unroll
-        for (int q = 0; q < 20; q++) v[q] += __uint_as_float(fm_from_next<8>(__float_as_uint(v[q])));
+        for (int q = 0; q < N; q++) v[q] += __uint_as_float(fm_from_next<1>(__float_as_uint(v[q])));
+    }
+    if (sh > 1) {
+#pragma unroll
+        for (int q = 0; q < N; q++) v[q] += __uint_as_float(fm_from_next<2>(__float_as_uint(v[q])));
+    }
+    if (sh > 2) {
+#pragma unroll
+        for (int q = 0; q < N; q++) v[q] += __uint_as_float(fm_from_next<4>(__float_as_uint(v[q])));
+    }
+    if (sh > 3) {
+#pragma unroll
+        for (int q = 0; q < N; q++) v[q] += __uint_as_float(fm_from_next<8>(__float_as_uint(v[q])));
     }
 }
-// this lane's group's 16 bits of a wavefront mask
-__device__ __forceinline__ uint32_t fm_gbits(uint64_t m, uint32_t g) { return (uint32_t)(m >> (16 * g)) & 0xffffu; }
 
-// Phase 3: leaf-node pairs, four per wavefront.  Each 16-lane group takes one
-// pair at a time (16 of the leaf's particles per chunk) and walks the
-// daughters of the internal node with the particle-node rules, with its own
-// stack of (first sibling, count, group lane mask) entries; a group whose walk
-// ends deposits its particles' sums and takes the wavefront's next pair.
-// Leaves opened in a step give particle pairs for the targets that opened
-// them only; these are spread one pair per lane over the whole wavefront.
 template <int KER, bool POT>
 __global__ __launch_bounds__(256) void k_fast_ln(FastArgs A, uint32_t npairs)
 {
-    __shared__ uint2 stk[4][4][FT_STK];     // (first sibling, count | group lane mask << 16)
-    __shared__ float red[4][4][20];
-    __shared__ uint4 tpos[4][64];           // targets (grid position, mass bits) for the leaf pairs
-    __shared__ float tacc[4][64][4];        // their pair sums
-    __shared__ float sacc[4][4][FT_SB][4];  // pair sums of the current source block of each group
-    __shared__ uint2 gblk[4][4];            // each group's source block: first particle, count
-    __shared__ uint8_t trank[4][4][16];     // each group's open targets: rank -> lane in the group
+    __shared__ LnLds lds[4];
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    const uint32_t g = (uint32_t)lane >> 4, gl = (uint32_t)lane & 15u;
-    tacc[wv][lane][0] = tacc[wv][lane][1] = tacc[wv][lane][2] = tacc[wv][lane][3] = 0.f;
-    for (uint32_t v = (uint32_t)lane; v < 4u * FT_SB * 4u; v += 64u) (&sacc[wv][0][0][0])[v] = 0.f;
+    LnLds &W = lds[wv];
     // this wavefront's contiguous share of the pairs
     const uint32_t nw = gridDim.x * 4, wid = blockIdx.x * 4 + wv;
     const uint32_t per = (npairs + nw - 1) / nw;
-    uint32_t next = min(npairs, wid * per);  // wavefront-uniform
-    const uint32_t end = min(npairs, next + per);
-    // group state (uniform within a group)
-    int sp = 0;
-    uint32_t ja = 0, na = 0, c0 = 0, tb = 0;
-    // lane state: one target particle
-    uint32_t t = 0;
-    bool act = false;
-    uint4 me = make_uint4(0u, 0u, 0u, 0u);
-    float mt = 0.f, fx = 0.f, fy = 0.f, fz = 0.f, fp = 0.f;
+    const uint32_t beg = min(npairs, wid * per), end = min(npairs, beg + per);
+    FlStack N{W.nfirst, W.ncount, W.nmask, FL_CAP, 0u}, L{W.lfirst, W.lcount, W.lmask, FL_LCAP, 0u};
     uint32_t n_pp = 0, n_pn = 0;
+    const uint32_t g = (uint32_t)lane / FL_TGT, gl = (uint32_t)lane % FL_TGT;
+    // each group of 16 lanes loads one pair (16 of its leaf's particles)
+    uint32_t next = beg, ja = 0, na = 0, c0 = 0, cf = 0, cn = 0;
     for (;;) {
-        // ---- groups whose walk ended: deposit, then the next chunk of the pair or the next pair
-        const bool done = sp == 0;
-        if (done && act) fm_deposit<POT>(A, t, fx, fy, fz, fp);
-        if (done) fx = fy = fz = fp = 0.f;
-        const bool more = done && c0 + 16 < na;
-        if (more) c0 += 16;
-        const bool want = done && !more;
-        const uint64_t wm = fm_ballot(want && gl == 0);  // one bit per group that needs a pair
-        const uint32_t k = next + (uint32_t)__builtin_popcountll(wm & ((1ull << (16 * g)) - 1ull));
-        next = min(end, next + (uint32_t)__builtin_popcountll(wm));
-        bool start = more;
-        if (want) {
-            if (k < end) {
-                const uint2 pr = A.ln[k];
-                ja = A.wn[pr.x].next;
-                na = A.wn[pr.x].num;
-                tb = pr.y;
-                c0 = 0;
-                start = true;
+        {
+            const bool more = c0 + FL_TGT < na;
+            const uint64_t wm = fm_ballot(!more && gl == 0);  // one bit per group that needs a pair
+            const uint32_t k = next + (uint32_t)__builtin_popcountll(wm & ((1ull << (FL_TGT * g)) - 1ull));
+            next = min(end, next + (uint32_t)__builtin_popcountll(wm));
+            if (more) {
+                c0 += FL_TGT;
             } else {
-                na = 0;
-                c0 = 0;
-            }
-        }
-        if (start) {
-            t = ja + c0 + gl;
-            act = c0 + gl < na;
-            me = A.parts[act ? t : ja];
-            mt = act ? __uint_as_float(me.w) : 0.f;
-        } else if (done) {
-            act = false;
-        }
-        const uint32_t am = fm_gbits(fm_ballot(act), g);
-        if (start) {
-            if (gl == 0) stk[wv][g][0] = make_uint2(A.wn[tb].next, A.wn[tb].num | (am << 16));
-            sp = 1;
-        }
-        if (!fm_ballot(sp > 0)) break;
-        fm_sync();
-        // ---- one step of every live group's walk
-        const bool live = sp > 0;
-        uint2 e = make_uint2(0u, 0u);
-        if (live) e = stk[wv][g][sp - 1];
-        const uint32_t node = e.x, cnt = e.y & 0xffffu, gm = e.y >> 16;
-        if (live) {
-            if (cnt > 1) {
-                if (gl == 0) stk[wv][g][sp - 1] = make_uint2(node + 1, (cnt - 1) | (gm << 16));
-            } else {
-                sp--;
-            }
-        }
-        const WNode w = A.wn[live ? node : 0u];
-        const bool mine = live && ((gm >> gl) & 1u);
-        const int lev = (int)(w.meta & 0xffu);
-        // particle (l = 0) against the node: the rules of fm_classify
-        float g2;
-        const bool touching = fm_cube_gap(me.x, me.y, me.z, w.gx, w.gy, w.gz, 1ull << (A.S - lev - 1), A.unit, g2);
-        const bool drop = A.kernel == 1 && g2 > A.rcut2;
-        const float r[3] = {(float)(int32_t)(w.cx - me.x) * A.unit, (float)(int32_t)(w.cy - me.y) * A.unit,
-                            (float)(int32_t)(w.cz - me.z) * A.unit};
-        const float r2 = r[0] * r[0] + r[1] * r[1] + r[2] * r[2];
-        const float l = ldexpf(A.box, -lev);
-        const float a_t = A.crit ? A.pseed[act ? t : ja] : 0.f, a_n = A.crit ? A.amin[live ? node : 0u] : 0.f;
-        const bool inter = mine && !drop && !touching &&
-                           fmm_accept(A.crit, A.theta2, A.alpha, 0.f, l, mt, w.mass, a_t, a_n, r2) && r2 >= A.h2;
-        const bool open = mine && !drop && !inter;
-        const uint64_t im = fm_ballot(inter);
-        if (im) {
-            float pf[20];
-#pragma unroll
-            for (int q = 0; q < 20; q++) pf[q] = 0.f;
-            if (inter) {
-                float g0, g1, g2, g3;
-                gfun_f(KER, r2, A.asplit, g0, g1, g2, g3);
-                // the node's field at the particle: a = -F1, phi = -F0
-                float f[20], q2[6], q3[10];
-#pragma unroll
-                for (int q = 0; q < 20; q++) f[q] = 0.f;
-#pragma unroll
-                for (int q = 0; q < 6; q++) q2[q] = w.q[q];
-                if (POT) {
-#pragma unroll
-                    for (int q = 0; q < 10; q++) q3[q] = A.q3[(size_t)node * 10 + q];
+                c0 = na = 0;
+                if (k < end) {
+                    const uint2 pr = A.ln[k];
+                    ja = A.wn[pr.x].next;
+                    na = A.wn[pr.x].num;
+                    cf = A.wn[pr.y].next;
+                    cn = A.wn[pr.y].num;
                 }
-                add_field_f(f, r, g0, g1, g2, g3, w.mass, q2, POT ? q3 : nullptr);
-                float Dp[20];
-                if constexpr (KER == 2) {
-                    ew_d20(A.ew, A.ew_n, A.ew_h, A.ew_hinv, r[0], r[1], r[2], Dp);
-                    sub_field_psi(f, Dp, w.mass, q2, POT ? q3 : nullptr);
-                }
-                fx -= f[1];
-                fy -= f[2];
-                fz -= f[3];
-                if (POT) fp -= f[0];
-                // the particle's field at the node (source at -r)
-                const float mr[3] = {-r[0], -r[1], -r[2]};
-                add_field_f(pf, mr, g0, g1, g2, g3, mt, nullptr, nullptr);
-                if constexpr (KER == 2) {
-                    psi_mirror(Dp);
-                    sub_field_psi(pf, Dp, mt, nullptr, nullptr);
-                }
-                n_pn++;
             }
-            // only the lanes in im hold nonzero values: within each group, lanes 0-3, 0-7 or all 16
-            const uint32_t span = (im & 0xff00ff00ff00ff00ull) ? 16u : (im & 0xfff0fff0fff0fff0ull) ? 8u : 4u;
-            fm_gsum20(pf, span);  // read by lane 0 of the group
-            const bool gi = fm_gbits(im, g) != 0;
-            if (gi && gl == 0) {
-#pragma unroll
-                for (int q = 0; q < 20; q++) red[wv][g][q] = pf[q];
+            const uint32_t kt = min(na - c0, (uint32_t)FL_TGT);
+            const uint64_t am = fm_ballot(gl == 0 && kt > 0);
+            if (!am) break;
+            if (gl < kt) W.tgt[lane] = A.parts[ja + c0 + gl];
+            *reinterpret_cast<float4 *>(W.tacc[lane]) = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (gl == 0) {
+                W.tbase[g] = ja + c0;
+                if (kt > 0) {
+                    const uint32_t q = fm_below(am);
+                    N.first[q] = cf;
+                    N.count[q] = cn;
+                    N.mask[q] = ((1u << kt) - 1u) | g << 16;
+                }
             }
+            N.n = (uint32_t)__builtin_popcountll(am);
+            uint32_t pend = 0;  // (source, target) pairs of the opened leaves
             fm_sync();
-            if (gi) {
-                atomicAdd(&A.F[(size_t)node * 20 + gl], red[wv][g][gl]);
-                if (gl < 4) atomicAdd(&A.F[(size_t)node * 20 + 16 + gl], red[wv][g][16 + gl]);
-            }
-            fm_sync();
-        }
-        const uint64_t om = fm_ballot(open);
-        if (om) {
-            const uint32_t go = fm_gbits(om, g);
-            const bool gleaf = go && (w.meta & WN_LEAF);
-            const uint64_t lm = fm_ballot(gleaf);
-            if (lm) {
-                // particle pairs with the opened leaves of the wavefront's groups, one pair per
-                // lane: group g pairs its open targets with the leaf's sources in blocks of
-                // FT_SB; both sides are summed in LDS and the sources' sums deposited per block
-                const uint32_t om16 = fm_gbits(om, g);
-                if (open && gleaf) {
-                    trank[wv][g][__builtin_popcount(om16 & ((1u << gl) - 1u))] = (uint8_t)gl;
-                    tpos[wv][lane] = make_uint4(me.x, me.y, me.z, __float_as_uint(mt));
-                }
-                // the longest opened leaf of the wavefront
-                // (the node and gleaf are uniform within a group: one lane of each group suffices)
-                const uint32_t nl = gleaf ? w.num : 0u;
-                const uint32_t nmax = max(max((uint32_t)__builtin_amdgcn_readlane((int)nl, 0),
-                                              (uint32_t)__builtin_amdgcn_readlane((int)nl, 16)),
-                                          max((uint32_t)__builtin_amdgcn_readlane((int)nl, 32),
-                                              (uint32_t)__builtin_amdgcn_readlane((int)nl, 48)));
-                const uint32_t gk = gleaf ? (uint32_t)__builtin_popcount(om16) : 0u;
-                for (uint32_t b0 = 0; b0 < nmax; b0 += FT_SB) {
-                    const uint32_t nb = gleaf && b0 < w.num ? min(w.num - b0, (uint32_t)FT_SB) : 0u;
-                    // pair ranges of the four groups (uniform)
-                    const uint32_t P0 = __builtin_amdgcn_readlane((int)(gk * nb), 0),
-                                   P1 = __builtin_amdgcn_readlane((int)(gk * nb), 16),
-                                   P2 = __builtin_amdgcn_readlane((int)(gk * nb), 32),
-                                   P3 = __builtin_amdgcn_readlane((int)(gk * nb), 48);
-                    if (gl == 0) gblk[wv][g] = make_uint2(w.next + b0, nb);
-                    fm_sync();
-                    const uint32_t e1 = P0, e2 = e1 + P1, e3 = e2 + P2, ptot = e3 + P3;
-                    for (uint32_t base = 0; base < ptot; base += 64) {
-                        const uint32_t p = base + (uint32_t)lane;
-                        if (p < ptot) {
-                            const uint32_t gg = (p >= e1 ? 1u : 0u) + (p >= e2 ? 1u : 0u) + (p >= e3 ? 1u : 0u);
-                            const uint32_t pl = p - (gg == 0 ? 0u : gg == 1 ? e1 : gg == 2 ? e2 : e3);
-                            const uint2 gb = gblk[wv][gg];
-                            // pl = rank nb + k, k < nb <= FT_SB
-                            uint32_t rk = (uint32_t)((float)pl * __builtin_amdgcn_rcpf((float)gb.y));
-                            if (rk * gb.y > pl) rk--;
-                            else if ((rk + 1u) * gb.y <= pl) rk++;
-                            const uint32_t ks = pl - rk * gb.y;
-                            const uint32_t tl = 16u * gg + trank[wv][gg][rk];
-                            const uint4 T = tpos[wv][tl];
-                            const uint4 src = A.parts[gb.x + ks];
-                            const float sx = (float)(int32_t)(src.x - T.x) * A.unit;
-                            const float sy = (float)(int32_t)(src.y - T.y) * A.unit;
-                            const float sz = (float)(int32_t)(src.z - T.z) * A.unit;
-                            float K, W;
-                            pair_kernel<KER == 2 ? 0 : KER, POT>(sx * sx + sy * sy + sz * sz, A.asplit, A.h2,
-                                                                 A.hinv, K, W);
-                            // force per unit source mass on the target (the source gets minus it)
-                            float vx = K * sx, vy = K * sy, vz = K * sz;
-                            if constexpr (KER == 2) {
-                                float ex, ey, ez, ep = 0.f;
-                                ew_grad<POT>(A.ew, A.ew_n, A.ew_h, A.ew_hinv, sx, sy, sz, ex, ey, ez, ep);
-                                vx += ex;
-                                vy += ey;
-                                vz += ez;
-                                if (POT) W -= ep;
+            while (N.n || L.n) {
+                uint32_t nc, sh;
+                const bool nodes = N.n && pend < 64;
+                fl_take(nodes ? N : L, nodes && N.n > FL_DEEP ? 1u : (uint32_t)FL_TOP, W.ch, lane, nc, sh);
+                const uint32_t ci = (uint32_t)lane >> sh, rank = (uint32_t)lane & ((1u << sh) - 1u);
+                const uint4 C = W.ch[ci];
+                const bool valid = ci < nc && rank < (C.y & 0xffu);
+                const uint32_t t =
+                    valid ? (C.y >> 8) * FL_TGT + ((uint32_t)((((uint64_t)C.w << 32) | C.z) >> (4 * rank)) & 15u) : 0u;
+                const uint32_t id = ci < nc ? C.x : 0u;
+                const uint4 T = W.tgt[t];
+                const float mt = __uint_as_float(T.w);
+                if (nodes) {
+                    const WNode w = A.wn[id];
+                    const int lev = (int)(w.meta & 0xffu);
+                    // particle (l = 0) against the node: the rules of fm_classify
+                    float gap2;
+                    const bool touching = fm_cube_gap(T.x, T.y, T.z, w.gx, w.gy, w.gz, 1ull << (A.S - lev - 1), A.unit, gap2);
+                    const bool drop = A.kernel == 1 && gap2 > A.rcut2;
+                    const float r[3] = {(float)(int32_t)(w.cx - T.x) * A.unit, (float)(int32_t)(w.cy - T.y) * A.unit,
+                                        (float)(int32_t)(w.cz - T.z) * A.unit};
+                    const float r2 = r[0] * r[0] + r[1] * r[1] + r[2] * r[2];
+                    const float l = ldexpf(A.box, -lev);
+                    const float a_t = A.crit && valid ? A.pseed[W.tbase[t / FL_TGT] + t % FL_TGT] : 0.f, a_n = A.crit ? A.amin[id] : 0.f;
+                    const bool inter = valid && !drop && !touching &&
+                                       fmm_accept(A.crit, A.theta2, A.alpha, 0.f, l, mt, w.mass, a_t, a_n, r2) && r2 >= A.h2;
+                    const bool open = valid && !drop && !inter;
+                    const uint64_t im = fm_ballot(inter);
+                    if (im) {
+                        float pf[20];
+#pragma unroll
+                        for (int q = 0; q < 20; q++) pf[q] = 0.f;
+                        if (inter) {
+                            float g0, g1, g2, g3;
+                            gfun_f(KER, r2, A.asplit, g0, g1, g2, g3);
+                            // the node's field at the particle: a = -F1, phi = -F0
+                            float f[20], q2[6], q3[10];
+#pragma unroll
+                            for (int q = 0; q < 20; q++) f[q] = 0.f;
+#pragma unroll
+                            for (int q = 0; q < 6; q++) q2[q] = w.q[q];
+                            if (POT) {
+#pragma unroll
+                                for (int q = 0; q < 10; q++) q3[q] = A.q3[(size_t)id * 10 + q];
                             }
-                            const float ms = __uint_as_float(src.w), mo = __uint_as_float(T.w);
-                            atomicAdd(&tacc[wv][tl][0], ms * vx);
-                            atomicAdd(&tacc[wv][tl][1], ms * vy);
-                            atomicAdd(&tacc[wv][tl][2], ms * vz);
-                            if (POT) atomicAdd(&tacc[wv][tl][3], -ms * W);
-                            atomicAdd(&sacc[wv][gg][ks][0], -mo * vx);
-                            atomicAdd(&sacc[wv][gg][ks][1], -mo * vy);
-                            atomicAdd(&sacc[wv][gg][ks][2], -mo * vz);
-                            if (POT) atomicAdd(&sacc[wv][gg][ks][3], -mo * W);
+                            add_field_f(f, r, g0, g1, g2, g3, w.mass, q2, POT ? q3 : nullptr);
+                            float Dp[20];
+                            if constexpr (KER == 2) {
+                                ew_d20(A.ew, A.ew_n, A.ew_h, A.ew_hinv, r[0], r[1], r[2], Dp);
+                                sub_field_psi(f, Dp, w.mass, q2, POT ? q3 : nullptr);
+                            }
+                            atomicAdd(&W.tacc[t][0], -f[1]);
+                            atomicAdd(&W.tacc[t][1], -f[2]);
+                            atomicAdd(&W.tacc[t][2], -f[3]);
+                            if (POT) atomicAdd(&W.tacc[t][3], -f[0]);
+                            // the particle's field at the node (source at -r)
+                            const float mr[3] = {-r[0], -r[1], -r[2]};
+                            add_field_f(pf, mr, g0, g1, g2, g3, mt, nullptr, nullptr);
+                            if constexpr (KER == 2) {
+                                psi_mirror(Dp);
+                                sub_field_psi(pf, Dp, mt, nullptr, nullptr);
+                            }
+                            n_pn++;
+                        }
+                        fl_sum<20>(pf, sh);
+                        for (uint32_t b = 0; b < nc; b += FL_RED) {
+                            if (rank == 0 && ci - b < FL_RED) {
+#pragma unroll
+                                for (int q = 0; q < 20; q++) W.red[ci - b][q] = pf[q];
+                            }
+                            fm_sync();
+                            const uint32_t nv = min(nc - b, (uint32_t)FL_RED) * 20u;
+                            for (uint32_t v = (uint32_t)lane; v < nv; v += 64) {
+                                const uint32_t c = v / 20u, q = v - 20u * c;
+                                // nodes without an interacting target have a zero sum
+                                if (im >> ((b + c) << sh) & ((2ull << ((1u << sh) - 1u)) - 1ull))
+                                    atomicAdd(&A.F[(size_t)W.ch[b + c].x * 20 + q], W.red[c][q]);
+                            }
+                            fm_sync();
                         }
                     }
-                    fm_sync();
-                    // the sources' sums of this block, cleared for the next
-                    if (gk) {
-                        for (uint32_t kk = gl; kk < nb; kk += 16) {
-                            float *sa = sacc[wv][g][kk];
-                            fm_deposit<POT>(A, w.next + b0 + kk, sa[0], sa[1], sa[2], sa[3]);
-                            sa[0] = sa[1] = sa[2] = sa[3] = 0.f;
-                        }
+                    const bool leaf = (w.meta & WN_LEAF) != 0;
+                    const bool oleaf = open && leaf, onode = open && !leaf;
+                    if (oleaf) n_pp += w.num;
+                    fl_push(L, oleaf, t, w.next, w.num, sh, lane, A.flags);
+                    fl_push(N, onode, t, w.next, w.num, sh, lane, A.flags);
+                    // pairs added: the opened leaves' particles, once per asking target
+                    uint32_t add = oleaf ? w.num : 0u;
+                    if (fm_ballot(oleaf)) {
+                        for (int off = 32; off > 0; off >>= 1) add += (uint32_t)__shfl_xor((int)add, off);
+                        pend += fm_uni(add);
                     }
+                } else {
+                    // one (source, target) pair per slot; the source's sum over its targets is deposited
+                    const uint4 src = A.parts[id];
+                    float v[4] = {0.f, 0.f, 0.f, 0.f};
+                    if (valid) {
+                        const float sx = (float)(int32_t)(src.x - T.x) * A.unit;
+                        const float sy = (float)(int32_t)(src.y - T.y) * A.unit;
+                        const float sz = (float)(int32_t)(src.z - T.z) * A.unit;
+                        float K, P;
+                        pair_kernel<KER == 2 ? 0 : KER, POT>(sx * sx + sy * sy + sz * sz, A.asplit, A.h2, A.hinv, K, P);
+                        // force per unit source mass on the target (the source gets minus it)
+                        float vx = K * sx, vy = K * sy, vz = K * sz;
+                        if constexpr (KER == 2) {
+                            float ex, ey, ez, ep = 0.f;
+                            ew_grad<POT>(A.ew, A.ew_n, A.ew_h, A.ew_hinv, sx, sy, sz, ex, ey, ez, ep);
+                            vx += ex;
+                            vy += ey;
+                            vz += ez;
+                            if (POT) P -= ep;
+                        }
+                        const float ms = __uint_as_float(src.w);
+                        atomicAdd(&W.tacc[t][0], ms * vx);
+                        atomicAdd(&W.tacc[t][1], ms * vy);
+                        atomicAdd(&W.tacc[t][2], ms * vz);
+                        if (POT) atomicAdd(&W.tacc[t][3], -ms * P);
+                        v[0] = -mt * vx;
+                        v[1] = -mt * vy;
+                        v[2] = -mt * vz;
+                        if (POT) v[3] = -mt * P;
+                    }
+                    pend -= (uint32_t)__builtin_popcountll(fm_ballot(valid));
+                    fl_sum<POT ? 4 : 3>(v, sh);
+                    if (rank == 0 && ci < nc) fm_deposit<POT>(A, id, v[0], v[1], v[2], v[3]);
                     fm_sync();
                 }
-                // the targets' sums into their registers
-                fx += tacc[wv][lane][0];
-                fy += tacc[wv][lane][1];
-                fz += tacc[wv][lane][2];
-                if (POT) fp += tacc[wv][lane][3];
-                tacc[wv][lane][0] = tacc[wv][lane][1] = tacc[wv][lane][2] = tacc[wv][lane][3] = 0.f;
-                if (open && gleaf) n_pp += w.num;
             }
-            if (go && !gleaf && sp < FT_STK) {
-                if (gl == 0) stk[wv][g][sp] = make_uint2(w.next, w.num | (go << 16));
-                sp++;
-            } else if (go && !gleaf && gl == 0) {
-                atomicOr(A.flags, G4_FLAG_FMM_STACK);  // one entry per level: never expected
-            }
+            fm_sync();
+            if (gl < kt)
+                fm_deposit<POT>(A, ja + c0 + gl, W.tacc[lane][0], W.tacc[lane][1], W.tacc[lane][2], W.tacc[lane][3]);
+            fm_sync();
         }
-        fm_sync();
     }
     // counters: one atomic per wavefront
     unsigned long long c_pp = n_pp, c_pn = n_pn;
