@@ -22,6 +22,7 @@ struct DirectArgs {
     int64_t nt;
     double unit, h, hinv, asplit, rskip2, rcut2, G, L;
     float near2;  // squared reach of a pair in grid steps, rounded up (kernel 1, or truncated sums)
+    uint32_t reach16;  // the reach in steps of 2^16 grid units, rounded up, plus one for the dropped bits (FAR)
     int truncate;
     double *ax, *ay, *az, *pot;
 };
@@ -131,26 +132,45 @@ __device__ __forceinline__ void direct_pair(const DirectArgs &A, double r2, doub
 // still fills the chip (one thread per target left 96 of 10^4 targets' 256
 // compute units idle), and the partial sums of the lanes close in a fixed order.
 //
-// FAR (a reach much smaller than the box): a pair beyond the reach adds nothing,
+// FAR (a reach below half the box side): a pair beyond the reach adds nothing,
 // and 99 of 100 are, but each heavy FP64 evaluation stalled all 64 lanes of its
-// wavefront.  The lanes test their pairs in FP32 on the grid, against a reach
-// rounded up, and list the near ones in LDS; lists are evaluated 64 at a time
-// with the exact FP64 test, so the terms of every sum are the same.  Bound by the
-// issue of the FP32 test (about 15 instructions a pair and wavefront).  10^4
-// targets of 10^6 sources: 288 -> 10.4 ms; all 50 k on themselves 24.8 -> 3.9, 8192 Newtonian 2.35 -> 0.18.
+// wavefront.  Three stages, each on full wavefronts, joined by lists in LDS:
+// * a source against all targets of the block at once, on the upper 16 bits of
+//   the coordinates, two targets per packed 16-bit instruction: with c = X - r
+//   the offset is within [-r, r] exactly if px - c <= 2r modulo 2^16, so the
+//   largest of the three axes decides, and the least of them over the targets
+//   (28 instructions for 8 targets; the FP32 test of every pair took 15 each);
+// * the sources near some target against every target, in FP32 on the grid
+//   against a reach rounded up;
+// * the near pairs with the exact FP64 test, so the terms of every sum are the
+//   same.  Near pairs of one target come together: their atomics go to SL sums
+//   per target (at one sum they took as long as the kernel functions).
+// 10^4 targets of 10^6 sources at a reach of 0.075 box sides: 288 ms with one
+// thread per target, 10.7 with the FP32 test of every pair and one sum, 4.3
+// with the packed test, 3.7 with both; all 50 k on themselves (reach 0.2) 24.8,
+// 3.85, 2.9, 2.3; 8192 Newtonian (no reach) 2.35 -> 0.18.  Bound by the packed test
+// where near pairs are few (2.9 ms at a reach of 0.02), then by erfc and exp in FP64.
+#define DIRECT_TB 8                       // most targets of a block
+#define DIRECT_STEP 4                     // sources of a lane per step, all loaded before the first is tested
+                                          // (10^4 of 10^6: 5.35 ms at 2, 4.93 at 4, 4.79 at 8; 50 k: 3.04, 2.96, 3.02)
 #define DIRECT_WINDOW ((int64_t)1 << 28)  // sources of one pass: a list entry holds the source and target in 32 bits
 
+typedef uint16_t us2 __attribute__((ext_vector_type(2)));
+
+// FAR needs 4 wavefronts per SIMD (128 VGPRs; 10^4 of 10^6: 3.7 ms, 5.0 at 3, 4.9 at 5, where the FP64 part spills)
 template <int KER, int TB, int NW, bool FAR>
-__global__ __launch_bounds__(64 * NW) void k_direct(const DirectArgs A)
+__global__ __launch_bounds__(64 * NW, FAR ? 4 : 1) void k_direct(const DirectArgs A)
 {
     constexpr uint32_t QCAP = 64 * TB + 64;  // pending pairs of a wavefront: < 64 left, 64 TB appended per step
-    __shared__ double acc[NW][TB][4];
+    constexpr int SL = FAR ? (NW < 16 ? 8 : 4) : 1;  // partial sums per wavefront and target
+    __shared__ double acc[NW][TB][4][SL];
     __shared__ uint32_t list[FAR ? NW : 1][FAR ? QCAP : 1];
+    __shared__ uint32_t seen[FAR ? NW : 1][FAR ? 64 + 64 * DIRECT_STEP : 1];  // pending sources
     __shared__ uint32_t tx[TB], ty[TB], tz[TB];
     __shared__ int64_t ti[TB];
     const int64_t q0 = blockIdx.x * (int64_t)TB;
     const int nt = (int)min((int64_t)TB, A.nt - q0);
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     if (threadIdx.x < TB) {
         const int64_t q = q0 + min((int)threadIdx.x, nt - 1);  // the last block repeats its last target
         const int64_t i = A.targets ? A.targets[q] : q;
@@ -159,27 +179,39 @@ __global__ __launch_bounds__(64 * NW) void k_direct(const DirectArgs A)
         ty[threadIdx.x] = A.y[i];
         tz[threadIdx.x] = A.z[i];
     }
-    for (int k = threadIdx.x; k < NW * TB * 4; k += 64 * NW) (&acc[0][0][0])[k] = 0.0;
+    for (int k = threadIdx.x; k < NW * TB * 4 * SL; k += 64 * NW) (&acc[0][0][0][0])[k] = 0.0;
     __syncthreads();
     uint32_t X[TB], Y[TB], Z[TB];
 #pragma unroll
     for (int t = 0; t < TB; t++) {
-        X[t] = tx[t];
-        Y[t] = ty[t];
-        Z[t] = tz[t];
+        // the same for every lane: scalar registers
+        X[t] = (uint32_t)__builtin_amdgcn_readfirstlane((int)tx[t]);
+        Y[t] = (uint32_t)__builtin_amdgcn_readfirstlane((int)ty[t]);
+        Z[t] = (uint32_t)__builtin_amdgcn_readfirstlane((int)tz[t]);
     }
     if constexpr (FAR) {
-        uint32_t *L = list[wv];
+        uint32_t *L = list[wv], *S = seen[wv];
+        // two targets per word: the upper 16 bits of their coordinates less the reach
+        constexpr int TP = (TB + 1) / 2;
+        us2 cx[TP], cy[TP], cz[TP];
+#pragma unroll
+        for (int t = 0; t < TP; t++) {
+            const int u = 2 * t, v = min(2 * t + 1, TB - 1);
+            const uint16_t r = (uint16_t)A.reach16;
+            cx[t] = us2{(uint16_t)((X[u] >> 16) - r), (uint16_t)((X[v] >> 16) - r)};
+            cy[t] = us2{(uint16_t)((Y[u] >> 16) - r), (uint16_t)((Y[v] >> 16) - r)};
+            cz[t] = us2{(uint16_t)((Z[u] >> 16) - r), (uint16_t)((Z[v] >> 16) - r)};
+        }
         for (int64_t w0 = 0; w0 < A.n; w0 += DIRECT_WINDOW) {
             const uint32_t wn = (uint32_t)min(DIRECT_WINDOW, A.n - w0);
             const uint32_t *sx = A.x + w0, *sy = A.y + w0, *sz = A.z + w0;
-            uint32_t cnt = 0;  // pending pairs (uniform)
+            uint32_t cnt = 0, ns = 0;  // pending pairs and sources (uniform)
             // the last `k` pending pairs, one per lane
             auto eval = [&](uint32_t k) {
                 __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
                 __builtin_amdgcn_wave_barrier();
                 if ((uint32_t)lane < k) {
-                    const uint32_t e = L[cnt - k + lane], j = e / 8, t = e % 8;
+                    const uint32_t e = L[cnt - k + lane], j = e / DIRECT_TB, t = e % DIRECT_TB;
                     if (w0 + j != ti[t]) {
                         const double dx = (double)(int32_t)(sx[j] - tx[t]) * A.unit;
                         const double dy = (double)(int32_t)(sy[j] - ty[t]) * A.unit;
@@ -189,10 +221,10 @@ __global__ __launch_bounds__(64 * NW) void k_direct(const DirectArgs A)
                             const double m = (double)A.m[w0 + j];
                             double K, W;
                             direct_pair<KER>(A, r2, K, W);
-                            __hip_atomic_fetch_add(&acc[wv][t][0], m * K * dx, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
-                            __hip_atomic_fetch_add(&acc[wv][t][1], m * K * dy, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
-                            __hip_atomic_fetch_add(&acc[wv][t][2], m * K * dz, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
-                            __hip_atomic_fetch_add(&acc[wv][t][3], -m * W, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+                            __hip_atomic_fetch_add(&acc[wv][t][0][lane % SL], m * K * dx, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+                            __hip_atomic_fetch_add(&acc[wv][t][1][lane % SL], m * K * dy, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+                            __hip_atomic_fetch_add(&acc[wv][t][2][lane % SL], m * K * dz, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+                            __hip_atomic_fetch_add(&acc[wv][t][3][lane % SL], -m * W, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
                         }
                     }
                 }
@@ -200,27 +232,61 @@ __global__ __launch_bounds__(64 * NW) void k_direct(const DirectArgs A)
                 __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
                 __builtin_amdgcn_wave_barrier();
             };
-            for (uint32_t b = wv * 64; b < wn; b += 64 * NW) {
-                const uint32_t j = b + lane;
-                const bool have = j < wn;
-                const uint32_t jl = have ? j : wn - 1;
-                const uint32_t px = sx[jl], py = sy[jl], pz = sz[jl];
+            // the last `k` pending sources, one per lane, against every target
+            auto pairs = [&](uint32_t k) {
+                __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+                const bool have = (uint32_t)lane < k;
+                const uint32_t j = S[ns - k + (have ? lane : 0)];
+                const uint32_t px = sx[j], py = sy[j], pz = sz[j];
 #pragma unroll
                 for (int t = 0; t < TB; t++) {
-                    const float dx = (float)(int32_t)(px - X[t]), dy = (float)(int32_t)(py - Y[t]),
-                                dz = (float)(int32_t)(pz - Z[t]);
+                    const float dx = (float)(int32_t)(px - tx[t]), dy = (float)(int32_t)(py - ty[t]),
+                                dz = (float)(int32_t)(pz - tz[t]);
                     const bool near = have && fmaf(dx, dx, fmaf(dy, dy, dz * dz)) <= A.near2;
                     const uint64_t m = __builtin_amdgcn_ballot_w64(near);
-                    if (m) {
+                    if (near)
+                        L[cnt + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u))] =
+                            j * DIRECT_TB + t;
+                    cnt += (uint32_t)__builtin_popcountll(m);
+                }
+                ns -= k;
+            };
+            for (uint32_t b = wv * (64 * DIRECT_STEP);; b += 64 * DIRECT_STEP * NW) {
+                const bool last = b >= wn;
+                if (!last) {
+                    uint32_t px[DIRECT_STEP], py[DIRECT_STEP], pz[DIRECT_STEP];
+#pragma unroll
+                    for (int u = 0; u < DIRECT_STEP; u++) {
+                        const uint32_t j = min(b + 64 * u + lane, wn - 1);
+                        px[u] = sx[j];
+                        py[u] = sy[j];
+                        pz[u] = sz[j];
+                    }
+#pragma unroll
+                    for (int u = 0; u < DIRECT_STEP; u++) {
+                        const uint32_t j = b + 64 * u + lane;
+                        const us2 hx = us2((uint16_t)(px[u] >> 16)), hy = us2((uint16_t)(py[u] >> 16)),
+                                  hz = us2((uint16_t)(pz[u] >> 16));
+                        us2 least = us2((uint16_t)0xffff);
+#pragma unroll
+                        for (int t = 0; t < TP; t++)
+                            least = __builtin_elementwise_min(
+                                least, __builtin_elementwise_max(hx - cx[t], __builtin_elementwise_max(hy - cy[t], hz - cz[t])));
+                        const bool near = j < wn && min((uint32_t)least.x, (uint32_t)least.y) <= 2u * A.reach16;
+                        const uint64_t m = __builtin_amdgcn_ballot_w64(near);
                         if (near)
-                            L[cnt + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u))] =
-                                j * 8 + t;
-                        cnt += (uint32_t)__builtin_popcountll(m);
+                            S[ns + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u))] = j;
+                        ns += (uint32_t)__builtin_popcountll(m);
                     }
                 }
-                while (cnt >= 64) eval(64);
+                // 64 pending sources at a time (in the end the rest): their pairs, and the pairs' terms
+                while (ns >= 64 || (last && ns + cnt)) {
+                    if (ns) pairs(min(ns, 64u));
+                    while (cnt >= 64 || (last && cnt)) eval(min(cnt, 64u));
+                }
+                if (last) break;
             }
-            if (cnt) eval(cnt);
         }
     } else {
         double s[TB][4];
@@ -251,14 +317,15 @@ __global__ __launch_bounds__(64 * NW) void k_direct(const DirectArgs A)
             for (int c = 0; c < 4; c++) {
                 double v = s[t][c];
                 for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
-                if (lane == 0) acc[wv][t][c] = v;
+                if (lane == 0) acc[wv][t][c][0] = v;
             }
     }
     __syncthreads();
     if (threadIdx.x < (unsigned)(4 * nt)) {
         const int t = threadIdx.x >> 2, c = threadIdx.x & 3;
         double v = 0.0;
-        for (int w = 0; w < NW; w++) v += acc[w][t][c];
+        for (int w = 0; w < NW; w++)
+            for (int k = 0; k < SL; k++) v += acc[w][t][c][k];
         double *out = c == 0 ? A.ax : c == 1 ? A.ay : c == 2 ? A.az : A.pot;
         if (out) out[q0 + t] = A.G * v;
     }
@@ -315,21 +382,26 @@ __global__ __launch_bounds__(DT) void k_direct_ewald(const DirectArgs A)
 template <int KER, int TB, bool FAR>
 static void launch_direct_tb(const DirectArgs &A, hipStream_t s)
 {
-    // few targets: larger blocks, so that a block's lanes are more of the chip
+    // few targets: larger blocks, so that a block's lanes are more of the chip and its near
+    // pairs, which differ much from block to block, more evenly spread (reach 0.075: 300
+    // targets of 10^6 0.66 ms at 16 wavefronts, 0.68 at 8, 0.97 at 4; 10^4 targets 4.92, 4.28, 4.91)
     const int64_t blocks = (A.nt + TB - 1) / TB;
     if (blocks < 1024) k_direct<KER, TB, 16, FAR><<<(unsigned)blocks, 1024, 0, s>>>(A);
-    else k_direct<KER, TB, 4, FAR><<<(unsigned)blocks, 256, 0, s>>>(A);
+    else k_direct<KER, TB, FAR ? 8 : 4, FAR><<<(unsigned)blocks, FAR ? 512 : 256, 0, s>>>(A);
 }
 
 // Targets per block: 8 (4 without lists, where the sums stay in registers)
-// spare most source loads; fewer where that would leave less than two blocks
-// per compute unit.  The lists pay where a pair is rarely near: a reach of at
-// most a third of the box side (an eighth to a sixth of the pairs of a uniform set).
+// spare most source tests; fewer where that would leave less than four blocks
+// per compute unit (5000 targets of 200 k, reach 0.2: 1.49 ms at 8, 1.30 at 4).
+// The lists pay at every reach that the packed test can hold, below half the
+// box side: 10^4 targets of 10^6 take 3.0 ms with and 24.6 without at a reach
+// of 0.02, 18.5 and 58.9 at 0.33, 39.9 and 59.4 at 0.49 (300 targets of 50 k
+// to 10^6 at 0.49: 12 % less with lists); beyond that a box has nothing to skip.
 template <int KER>
 static void launch_direct(const DirectArgs &A, double reach2, double box, hipStream_t s)
 {
-    if (reach2 * 9.0 <= box * box) {
-        if (A.nt >= 4096) launch_direct_tb<KER, 8, true>(A, s);
+    if (reach2 * 4.1 <= box * box) {
+        if (A.nt >= 8192) launch_direct_tb<KER, 8, true>(A, s);
         else if (A.nt >= 2048) launch_direct_tb<KER, 4, true>(A, s);
         else if (A.nt >= 1024) launch_direct_tb<KER, 2, true>(A, s);
         else launch_direct_tb<KER, 1, true>(A, s);
@@ -361,6 +433,8 @@ int g4_launch_direct(g4_ctx *ctx, const g4_particles *p, const g4_tree_params *t
     A.ax = ax; A.ay = ay; A.az = az; A.pot = pot;
     const double reach2 = std::min(A.rskip2, truncate ? A.rcut2 : 1e300);
     A.near2 = (float)(reach2 / (A.unit * A.unit)) * 1.00001f;
+    // at most 0.494 2^16 + 2 where the lists are used
+    A.reach16 = (uint32_t)std::min(sqrt((double)A.near2) / 65536.0 + 2.0, 32767.0);
     if (A.nt > 0 && wp->kernel == 2) k_direct_ewald<<<(unsigned)A.nt, DT, 0, ctx->stream>>>(A);
     else if (A.nt > 0 && wp->kernel == 1) launch_direct<1>(A, reach2, tp->box, ctx->stream);
     else if (A.nt > 0) launch_direct<0>(A, reach2, tp->box, ctx->stream);
