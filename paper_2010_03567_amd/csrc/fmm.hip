@@ -46,7 +46,9 @@
 #define FMM_NODES 12
 #define FMM_LEVELS 16
 #define FMM_WORDS (FMM_LEVELS + G4_MAXLEV + 1)
-#define FMM_CNT_BYTES 256
+#define FMM_STATS 64           // first word of the interaction counts
+#define FMM_STAT_SLOTS 32      // copies of them, each in a cache line of its own
+#define FMM_CNT_BYTES (4 * FMM_STATS + 128 * FMM_STAT_SLOTS)
 
 struct FmmArgs {
     const WNode *wn;
@@ -280,6 +282,27 @@ __device__ __forceinline__ void put(uint64_t *key, uint32_t *val, uint32_t at, c
 }
 
 
+// Adds a wavefront's interaction counts (this lane's part of them) to one of the copies
+// behind `stat`.  Atomics on one address take 4 to 5 ns each, one after the other, whoever
+// issues them: on one copy they were half the time of the leaf-node pass of 32 k particles.
+// (One per block instead made the wavefronts of a block wait for each other: 2^21 particles,
+// leaf pairs 1.44 -> 1.57 ms.)
+__device__ __forceinline__ void fmm_count(unsigned long long *stat, unsigned long long pp, unsigned long long pn,
+                                          unsigned long long nn)
+{
+    for (int off = 32; off > 0; off >>= 1) {
+        pp += __shfl_xor(pp, off);
+        pn += __shfl_xor(pn, off);
+        nn += __shfl_xor(nn, off);
+    }
+    if ((threadIdx.x & 63) == 0) {
+        unsigned long long *s = stat + (blockIdx.x * 4 + (threadIdx.x >> 6)) % FMM_STAT_SLOTS * 16;
+        if (pp) atomicAdd(&s[0], pp);
+        if (pn) atomicAdd(&s[1], pn);
+        if (nn) atomicAdd(&s[2], nn);
+    }
+}
+
 // Block-aggregated append to three counters at once (all 256 threads call it):
 // one atomic per counter and block instead of per wavefront, since every
 // block appends to the same three counters and same-address atomics are
@@ -402,16 +425,7 @@ __global__ __launch_bounds__(256) void k_fmm_traverse(FmmArgs A)
             break;
         }
     }
-    for (int off = 32; off > 0; off >>= 1) {
-        c_pp += __shfl_xor(c_pp, off);
-        c_pn += __shfl_xor(c_pn, off);
-        c_nn += __shfl_xor(c_nn, off);
-    }
-    if ((threadIdx.x & 63) == 0) {
-        if (c_pp) atomicAdd(&A.stat[0], c_pp);
-        if (c_pn) atomicAdd(&A.stat[1], c_pn);
-        if (c_nn) atomicAdd(&A.stat[2], c_nn);
-    }
+    fmm_count(A.stat, c_pp, c_pn, c_nn);
 }
 
 // the walk starts from the self-pair of every root (one root per box of a forest)
@@ -419,12 +433,13 @@ __global__ void k_fmm_init(uint32_t *cnt, uint2 *f0, unsigned long long *stat, c
 {
     const int b = blockIdx.x * blockDim.x + threadIdx.x;
     if (b < nroot) f0[b] = make_uint2((uint32_t)b, (uint32_t)b);
+    if (blockIdx.x == 0)
+        for (int k = b; k < FMM_STAT_SLOTS * 16; k += 256) stat[k] = 0;
     if (b == 0) {
         for (int k = 0; k < FMM_LEVELS; k++) cnt[k] = 0;
         cnt[FMM_FRONT] = (uint32_t)nroot;
         cnt[FMM_NODES] = C->node_count;
         for (int l = 0; l <= G4_MAXLEV; l++) cnt[FMM_LEVELS + l] = C->lvl_count[l];
-        stat[0] = stat[1] = stat[2] = 0;
     }
 }
 
@@ -746,9 +761,15 @@ __global__ void k_fmm_l2l(FmmArgs A, int level, float *__restrict__ F)
     }
 }
 
-__global__ void k_fmm_leafmap(const DevCounters *__restrict__ C, const WNode *__restrict__ wn,
-                              uint32_t *__restrict__ leafid)
+// leaf of every particle, and the walk's interaction counts into the counter block
+__global__ void k_fmm_leafmap(DevCounters *__restrict__ C, const WNode *__restrict__ wn, uint32_t *__restrict__ leafid,
+                              const unsigned long long *__restrict__ stat)
 {
+    if (blockIdx.x == 0 && threadIdx.x < 3) {
+        unsigned long long v = 0;
+        for (int k = 0; k < FMM_STAT_SLOTS; k++) v += stat[k * 16 + threadIdx.x];
+        C->stat[6 + threadIdx.x] = v;
+    }
     const uint32_t nn = C->node_count;
     for (uint32_t q = blockIdx.x * blockDim.x + threadIdx.x; q < nn; q += gridDim.x * blockDim.x) {
         const WNode w = wn[q];
@@ -904,7 +925,7 @@ __global__ __launch_bounds__(256) void k_fmm_particles(FmmArgs A, const uint32_t
 //  4. downward shift (the kernel above) and evaluation at the particles.
 // Summation order follows the scheduling of the atomics, so results agree
 // with the list-based path to round-off but are not bitwise reproducible.
-#define FP_SRC 512 // partner particles listed in LDS at a time by the leaf-pair kernel
+#define FP_SRC 128  // partner particles in LDS at a time (at 512 fewer wavefronts fit: 2^21 particles 1.4 -> 2.3 ms)
 #define FT_NC 2     // copies of the daughters' field sums in the node-pair passes
 
 __constant__ uint8_t c_tri[36][2] = {{0, 0}, {0, 1}, {1, 1}, {0, 2}, {1, 2}, {2, 2}, {0, 3}, {1, 3}, {2, 3}, {3, 3}, {0, 4}, {1, 4}, {2, 4}, {3, 4}, {4, 4}, {0, 5}, {1, 5}, {2, 5}, {3, 5}, {4, 5}, {5, 5}, {0, 6}, {1, 6}, {2, 6}, {3, 6}, {4, 6}, {5, 6}, {6, 6}, {0, 7}, {1, 7}, {2, 7}, {3, 7}, {4, 7}, {5, 7}, {6, 7}, {7, 7}};  // daughter pairs (i <= j) of a self pair, j-major
@@ -998,35 +1019,41 @@ __device__ __forceinline__ void st_push(Stage<CAP> &S, bool want, uint2 v)
     S.n += (uint32_t)__builtin_popcountll(m);
 }
 
-// write out cap - 64 pending pairs (or all, if final) to out[] behind counter.
+// write out CAP - 64 pending pairs to out[] behind counter if there are as many.
 // Every wavefront appends to the same counter, and same-address atomics are
 // serialised across the chip, so larger batches mean fewer of them.
 template <uint32_t CAP>
-__device__ __forceinline__ void st_flush(Stage<CAP> &S, bool final, uint2 *out, uint32_t *counter, uint32_t cap,
-                                         uint32_t *overflow)
+__device__ __forceinline__ void st_flush(Stage<CAP> &S, uint2 *out, uint32_t *counter, uint32_t cap, uint32_t *overflow)
 {
     const int lane = threadIdx.x & 63;
     constexpr uint32_t chunk = CAP - 64u;
-    while (S.n >= chunk || (final && S.n > 0)) {
-        const uint32_t k = min(S.n, chunk);
+    while (S.n >= chunk) {
         fm_sync();
         uint32_t base = 0;
-        if (lane == 0) base = atomicAdd(counter, k);
+        if (lane == 0) base = atomicAdd(counter, chunk);
         base = fm_uni(base);
 #pragma unroll
         for (uint32_t l0 = 0; l0 < chunk; l0 += 64u) {
             const uint32_t l = l0 + (uint32_t)lane;
-            if (l < k) {
-                if (base + l < cap) out[base + l] = S.buf[l];
-                else atomicOr(overflow, 1u);
-            }
+            if (base + l < cap) out[base + l] = S.buf[l];
+            else atomicOr(overflow, 1u);
         }
         // move the rest (< 64) to the front
-        const uint2 rest = (uint32_t)lane + k < S.n ? S.buf[lane + k] : make_uint2(0u, 0u);
+        const uint2 rest = (uint32_t)lane + chunk < S.n ? S.buf[lane + chunk] : make_uint2(0u, 0u);
         fm_sync();
-        if ((uint32_t)lane + k < S.n) S.buf[lane] = rest;
-        S.n -= k;
+        if ((uint32_t)lane + chunk < S.n) S.buf[lane] = rest;
+        S.n -= chunk;
         fm_sync();
+    }
+}
+
+// write out what is pending to out[base ..]
+template <uint32_t CAP>
+__device__ __forceinline__ void st_put(const Stage<CAP> &S, uint2 *out, uint32_t base, uint32_t cap, uint32_t *overflow)
+{
+    for (uint32_t l = threadIdx.x & 63; l < S.n; l += 64u) {
+        if (base + l < cap) out[base + l] = S.buf[l];
+        else atomicOr(overflow, 1u);
     }
 }
 
@@ -1057,8 +1084,13 @@ __global__ __launch_bounds__(256) void k_fast_open(FastArgs A)
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     float(*FL)[16][20] = Floc[wv];
     for (int v = lane; v < FT_NC * 320; v += 64) (&FL[0][0][0])[v] = 0.f;
+    // after an overflow the host retries with more room: decided once per block, since
+    // every wavefront of it must reach the barriers at the end
+    __shared__ uint32_t s_over, left[3][4], base3[3];
+    if (threadIdx.x == 0) s_over = A.cnt[4];
     if (blockIdx.x == 0 && threadIdx.x == 0) *A.cnext = 0;
-    if (A.cnt[4]) return;  // a list overflowed: the host retries with more room
+    __syncthreads();
+    if (s_over) return;
     const uint32_t nin = min(*A.cin, A.cap_pairs);
     uint32_t c_nn = 0;
     Stage<128> sf{sbf[wv], 0u}, sn{sbn[wv], 0u};
@@ -1237,14 +1269,32 @@ __global__ __launch_bounds__(256) void k_fast_open(FastArgs A)
         st_push(sf, (act == 3 && !l1) || (act == 2 && !l1 && !l2), pij);
         st_push(sl, act == 2 && l1 && l2, pij);
         st_push(sn, act == 2 && (l1 != l2), l1 ? pij : make_uint2(cb + j, ca + i));
-        st_flush(sf, false, A.fout, A.cout, A.cap_pairs, &A.cnt[4]);
-        st_flush(sl, false, A.ll, &A.cnt[2], A.cap_ll, &A.cnt[4]);
-        st_flush(sn, false, A.ln, &A.cnt[3], A.cap_ln, &A.cnt[4]);
+        st_flush(sf, A.fout, A.cout, A.cap_pairs, &A.cnt[4]);
+        st_flush(sl, A.ll, &A.cnt[2], A.cap_ll, &A.cnt[4]);
+        st_flush(sn, A.ln, &A.cnt[3], A.cap_ln, &A.cnt[4]);
     }
-    st_flush(sf, true, A.fout, A.cout, A.cap_pairs, &A.cnt[4]);
-    st_flush(sl, true, A.ll, &A.cnt[2], A.cap_ll, &A.cnt[4]);
-    st_flush(sn, true, A.ln, &A.cnt[3], A.cap_ln, &A.cnt[4]);
-    if (lane == 0 && c_nn) atomicAdd(&A.stat[2], (unsigned long long)c_nn);
+    // the rest of the block's four wavefronts, with one atomic per list
+    if (lane == 0) {
+        left[0][wv] = sf.n;
+        left[1][wv] = sl.n;
+        left[2][wv] = sn.n;
+    }
+    __syncthreads();
+    if (threadIdx.x < 3) {
+        const uint32_t *n = left[threadIdx.x], sum = n[0] + n[1] + n[2] + n[3];
+        base3[threadIdx.x] = sum ? atomicAdd(threadIdx.x == 0 ? A.cout : &A.cnt[1 + threadIdx.x], sum) : 0u;
+    }
+    __syncthreads();
+    uint32_t at[3];
+#pragma unroll
+    for (int k = 0; k < 3; k++) {
+        at[k] = base3[k];
+        for (int w = 0; w < wv; w++) at[k] += left[k][w];
+    }
+    st_put(sf, A.fout, at[0], A.cap_pairs, &A.cnt[4]);
+    st_put(sl, A.ll, at[1], A.cap_ll, &A.cnt[4]);
+    st_put(sn, A.ln, at[2], A.cap_ln, &A.cnt[4]);
+    fmm_count(A.stat, 0, 0, lane == 0 ? c_nn : 0u);
 }
 
 // ---- partner lists of the leaf pairs: count, exclusive scan, scatter
@@ -1386,11 +1436,15 @@ __device__ __forceinline__ void fm_pair(const FastArgs &A, const uint4 &t, const
 // Phase 2: all particle pairs of one leaf per wavefront.  Lane = (particle a,
 // stride slot k): slot k takes every S-th particle of each source leaf; the S
 // partial sums of a particle are added in LDS.  Writes acc (the first sum a
-// particle receives; phase 3 adds to it).
+// particle receives; phase 3 adds to it).  Bound by instruction issue, and by its longest
+// leaves at small sizes; partner records go through LDS, so that no pair waits for its
+// own gather: 2^21 particles, leaf 16, 1.60 -> 1.42 ms; 32 k (with the counts in many
+// copies) 0.14 -> 0.05 ms.  Four wavefronts to a leaf took 0.06 and 3.4 ms.
 template <int KER, bool POT>
 __global__ __launch_bounds__(256) void k_fast_pp(FastArgs A, uint32_t nnodes)
 {
     __shared__ float part[4][64][4];
+    __shared__ uint4 stage[4][FP_SRC];    // and their records
     __shared__ uint32_t srcs[4][FP_SRC];  // partner particles of the current window
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     unsigned long long n_pairs = 0;  // this lane's share of the pair count
@@ -1439,8 +1493,10 @@ __global__ __launch_bounds__(256) void k_fast_pp(FastArgs A, uint32_t nnodes)
                     const uint32_t lo = max(excl, w0), hi = min(excl + pn, w0 + wn);
                     for (uint32_t x = lo; x < hi; x++) srcs[wv][x - w0] = pj + (x - excl);
                     fm_sync();
+                    for (uint32_t x = (uint32_t)lane; x < wn; x += 64) stage[wv][x] = A.parts[srcs[wv][x]];
+                    fm_sync();
                     for (uint32_t s = (act ? k : wn); s < wn; s += S) {
-                        const uint4 src = A.parts[srcs[wv][s]];
+                        const uint4 src = stage[wv][s];
                         fm_pair<KER, POT>(A, me, src, __uint_as_float(src.w), fx, fy, fz, fp);
                     }
                     fm_sync();
@@ -1469,8 +1525,7 @@ __global__ __launch_bounds__(256) void k_fast_pp(FastArgs A, uint32_t nnodes)
             fm_sync();
         }
     }
-    for (int off = 32; off > 0; off >>= 1) n_pairs += __shfl_xor(n_pairs, off);
-    if (lane == 0 && n_pairs) atomicAdd(&A.stat[0], n_pairs);
+    fmm_count(A.stat, n_pairs, 0, 0);
 }
 
 template <bool POT>
@@ -1500,8 +1555,8 @@ __device__ __forceinline__ void fm_deposit(const FastArgs &A, uint32_t j, float 
 // wavefront or nothing else is left.
 // Bound by instruction issue (about 400 a step), with the chain of steps of the
 // longest pair at small sizes.  Groups of 16 lanes that each walked one node at a
-// time had 28 % of their lanes busy: 2^21 particles, leaf 16, 7.1 -> 5.7 ms; 32 k
-// 0.39 -> 0.23 ms.  Of the 5.7 the field atomics take 1.0, the target adds 0.5
+// time had 28 % of their lanes busy: 2^21 particles, leaf 16, 7.1 -> 5.6 ms; 32 k
+// 0.39 -> 0.11 ms.  Of the 5.6 the field atomics take 1.0, the target adds 0.5
 // (2 or 4 copies of them, or five wavefronts per SIMD instead of four: no gain).
 #define FL_TGT 16    // targets of a pair
 #define FL_PAIRS 4   // pairs a wavefront walks at a time
@@ -1811,16 +1866,7 @@ __global__ __launch_bounds__(256) void k_fast_ln(FastArgs A, uint32_t npairs)
             fm_sync();
         }
     }
-    // counters: one atomic per wavefront
-    unsigned long long c_pp = n_pp, c_pn = n_pn;
-    for (int off = 32; off > 0; off >>= 1) {
-        c_pp += __shfl_xor(c_pp, off);
-        c_pn += __shfl_xor(c_pn, off);
-    }
-    if (lane == 0) {
-        if (c_pp) atomicAdd(&A.stat[0], c_pp);
-        if (c_pn) atomicAdd(&A.stat[1], c_pn);
-    }
+    fmm_count(A.stat, n_pp, n_pn, 0);
 }
 
 // L2P at each particle plus its accumulated particle sums, written in caller order
@@ -1970,14 +2016,15 @@ static int fmm_seed_minima(g4_ctx *ctx, g4_tree *t, const g4_fmm_params *fp, flo
     return G4_OK;
 }
 
+// The pairs of a leaf or of a leaf-node pair vary widely in cost, so with more blocks than
+// the chip holds the last ones finish sooner; more than these cost more than they spread
+// (2^21 particles, leaf pairs: 1.48 ms at 8192 blocks, 1.42 at 16384, 1.42 at 32768;
+// leaf-node pairs: 5.64 at 4096, 5.55 at 8192, 5.58 at 16384).
 template <int KER, bool POT>
-// up to 4096 blocks of 4 wavefronts: the pairs of a leaf or of a leaf-node pair vary widely in cost,
-// and with more, smaller static shares the last wavefronts finish sooner (measured against 1024,
-// 2048 and 8192)
 static void launch_fast_particles(const FastArgs &A, uint32_t nnodes, uint32_t nln, hipStream_t s)
 {
-    k_fast_pp<KER, POT><<<(unsigned)std::min<uint64_t>(4096, ((uint64_t)nnodes + 3) / 4), 256, 0, s>>>(A, nnodes);
-    if (nln) k_fast_ln<KER, POT><<<(unsigned)std::min<uint64_t>(4096, ((uint64_t)nln + 3) / 4), 256, 0, s>>>(A, nln);
+    k_fast_pp<KER, POT><<<(unsigned)std::min<uint64_t>(16384, ((uint64_t)nnodes + 3) / 4), 256, 0, s>>>(A, nnodes);
+    if (nln) k_fast_ln<KER, POT><<<(unsigned)std::min<uint64_t>(8192, ((uint64_t)nln + 3) / 4), 256, 0, s>>>(A, nln);
 }
 
 // the frontier counters of one pass
@@ -2032,12 +2079,11 @@ static int fmm_fast(g4_ctx *ctx, g4_tree *t, const g4_fmm_params *fp, double fac
     A.plist = (uint32_t *)(b + L.plist);
     A.F = (float *)(b + L.F);
     A.acc = (double *)(b + L.acc);
-    A.stat = t->ctr->stat + 6;
+    A.stat = (unsigned long long *)(A.cnt + FMM_STATS);
     A.flags = &t->ctr->flags;
     uint2 *fr[2] = {(uint2 *)(b + L.f0), (uint2 *)(b + L.f1)};
     if ((uint64_t)t->nbox > L.cap_pairs) return g4_set_err(ctx, G4_ENOMEM, "fmm frontier smaller than the root count");
     if (int zst = g4_launch_zero(ctx, A.cnt, FMM_CNT_BYTES)) return zst;
-    if (int zst = g4_launch_zero(ctx, A.stat, 3 * sizeof(unsigned long long))) return zst;
     if (int zst = g4_launch_zero(ctx, A.F, (size_t)t->cap * 20 * 4)) return zst;
     A.fin = fr[1];
     A.fout = fr[0];
@@ -2100,7 +2146,7 @@ static int fmm_fast(g4_ctx *ctx, g4_tree *t, const g4_fmm_params *fp, double fac
     const int maxd = t->tp.max_depth;
     for (int l = 1; l <= maxd && levels[l]; l++) k_fmm_l2l<<<l2l_grid(levels[l]), 256, 0, s>>>(D, l, A.F);
     uint32_t *leafid = (uint32_t *)(b + L.leafid);
-    k_fmm_leafmap<<<(unsigned)std::min<uint32_t>(65535, (nnodes + 255) / 256), 256, 0, s>>>(t->ctr, t->wn, leafid);
+    k_fmm_leafmap<<<(unsigned)std::min<uint32_t>(65535, (nnodes + 255) / 256), 256, 0, s>>>(t->ctr, t->wn, leafid, A.stat);
     const unsigned pb = (unsigned)((t->n + 255) / 256);
     if (P) k_fast_finish<true><<<pb, 256, 0, s>>>(A, leafid, t->perm1, t->n, fp->G, ax, ay, az, pot);
     else k_fast_finish<false><<<pb, 256, 0, s>>>(A, leafid, t->perm1, t->n, fp->G, ax, ay, az, pot);
@@ -2171,7 +2217,7 @@ int g4_launch_fmm(g4_ctx *ctx, g4_tree *t, const g4_fmm_params *fp, double facto
     A.pval = (uint32_t *)(b + L.pval);
     A.cap_part = L.cap_part;
     A.bfirst = t->bfirst;
-    A.stat = t->ctr->stat + 6;
+    A.stat = (unsigned long long *)(A.cnt + FMM_STATS);
     uint2 *fr[2] = {(uint2 *)(b + L.f0), (uint2 *)(b + L.f1)};
     if ((uint64_t)t->nbox > L.cap_pairs) return g4_set_err(ctx, G4_ENOMEM, "fmm frontier smaller than the root count");
     k_fmm_init<<<(t->nbox + 255) / 256, 256, 0, s>>>(A.cnt, fr[0], A.stat, t->ctr, t->nbox);
@@ -2235,7 +2281,7 @@ int g4_launch_fmm(g4_ctx *ctx, g4_tree *t, const g4_fmm_params *fp, double facto
     const int maxd = t->tp.max_depth;
     for (int l = 1; l <= maxd && levels[l]; l++) k_fmm_l2l<<<l2l_grid(levels[l]), 256, 0, s>>>(A, l, F);
     uint32_t *leafid = (uint32_t *)(b + L.leafid);
-    k_fmm_leafmap<<<(unsigned)((nn_host + 255) / 256), 256, 0, s>>>(t->ctr, t->wn, leafid);
+    k_fmm_leafmap<<<(unsigned)((nn_host + 255) / 256), 256, 0, s>>>(t->ctr, t->wn, leafid, A.stat);
     const unsigned pb = (unsigned)((t->n + 15) / 16);
     if (fp->kernel == 2) {
         if (pot) k_fmm_particles<2, true><<<pb, 256, 0, s>>>(A, pstart, pend, F, leafid, t->perm1, t->n, fp->G, ax, ay, az, pot);
