@@ -38,15 +38,19 @@
 #define ENT_IDX(e) ((e) & 0x3fffffffu)
 #define ENT_TYPE(e) ((e) & 0xc0000000u)
 
-// Counter words of a call: [2..4] lists and overflow, three frontier sizes that
-// take turns as in, out and cleared (so that no launch rotates them between
-// passes), and the tree's node count and level sizes, so that one copy brings
-// the host all it asks for.
-#define FMM_FRONT 8
+// Counter words of a call: overflow, the tree's node count and level sizes, the
+// lengths of the two lists and three frontier sizes that take turns as in, out
+// and cleared (so that no launch rotates them between passes); one copy brings
+// the host all it asks for.  What is added to during a pass has a cache line of
+// its own: atomics on one line follow each other, and every wavefront appends.
+#define FMM_OVER 4
 #define FMM_NODES 12
 #define FMM_LEVELS 16
-#define FMM_WORDS (FMM_LEVELS + G4_MAXLEV + 1)
-#define FMM_STATS 64           // first word of the interaction counts
+#define FMM_LIST0 64    // leaf pairs; node list of the reproducible mode
+#define FMM_LIST1 96    // leaf-node pairs; particle list of the reproducible mode
+#define FMM_FRONT 128   // and 32, 64 words further
+#define FMM_WORDS (FMM_FRONT + 65)
+#define FMM_STATS 256   // first word of the interaction counts
 #define FMM_STAT_SLOTS 32      // copies of them, each in a cache line of its own
 #define FMM_CNT_BYTES (4 * FMM_STATS + 128 * FMM_STAT_SLOTS)
 
@@ -327,13 +331,10 @@ __device__ __forceinline__ uint3 block_append3(uint32_t *c0, uint32_t *c1, uint3
         wsum[wv][2] = i2;
     }
     __syncthreads();
-    if (threadIdx.x == 0) {
-        const uint32_t t0 = wsum[0][0] + wsum[1][0] + wsum[2][0] + wsum[3][0];
-        const uint32_t t1 = wsum[0][1] + wsum[1][1] + wsum[2][1] + wsum[3][1];
-        const uint32_t t2 = wsum[0][2] + wsum[1][2] + wsum[2][2] + wsum[3][2];
-        base[0] = t0 ? atomicAdd(c0, t0) : 0u;
-        base[1] = t1 ? atomicAdd(c1, t1) : 0u;
-        base[2] = t2 ? atomicAdd(c2, t2) : 0u;
+    if (threadIdx.x < 3) {
+        const int k = threadIdx.x;
+        const uint32_t sum = wsum[0][k] + wsum[1][k] + wsum[2][k] + wsum[3][k];
+        base[k] = sum ? atomicAdd(k == 0 ? c0 : k == 1 ? c1 : c2, sum) : 0u;
     }
     __syncthreads();
     uint32_t b0 = base[0], b1 = base[1], b2 = base[2];
@@ -351,7 +352,7 @@ __global__ __launch_bounds__(256) void k_fmm_traverse(FmmArgs A)
     // after an overflow the lists are incomplete: stop touching them (decided once per
     // block, since every thread of the block must reach the barriers of the appends)
     __shared__ uint32_t s_over;
-    if (threadIdx.x == 0) s_over = A.cnt[4];
+    if (threadIdx.x == 0) s_over = A.cnt[FMM_OVER];
     if (blockIdx.x == 0 && threadIdx.x == 0) *A.cnext = 0;
     __syncthreads();
     if (s_over) return;
@@ -368,7 +369,7 @@ __global__ __launch_bounds__(256) void k_fmm_traverse(FmmArgs A)
             const uint2 pr = A.fin[t];
             X = classify(A, pr.x, pr.y);
         }
-        const uint3 off3 = block_append3(A.cout, &A.cnt[2], &A.cnt[3], X.n_pairs, X.n_node, X.n_part);
+        const uint3 off3 = block_append3(A.cout, &A.cnt[FMM_LIST0], &A.cnt[FMM_LIST1], X.n_pairs, X.n_node, X.n_part);
         const uint32_t op = off3.x, on = off3.y, ok = off3.z;
         if (X.kind == ACT_PP) c_pp += 1;
         if (X.kind == ACT_OPEN_PP) c_pp += (unsigned long long)X.na * X.nb;
@@ -378,7 +379,7 @@ __global__ __launch_bounds__(256) void k_fmm_traverse(FmmArgs A)
         if (t >= nin) continue;
         if ((uint64_t)op + X.n_pairs > A.cap_pairs || (uint64_t)on + X.n_node > A.cap_node ||
             (uint64_t)ok + X.n_part > A.cap_part) {
-            atomicOr(&A.cnt[4], 1u);
+            atomicOr(&A.cnt[FMM_OVER], 1u);
             continue;
         }
         switch (X.kind) {
@@ -433,10 +434,11 @@ __global__ void k_fmm_init(uint32_t *cnt, uint2 *f0, unsigned long long *stat, c
 {
     const int b = blockIdx.x * blockDim.x + threadIdx.x;
     if (b < nroot) f0[b] = make_uint2((uint32_t)b, (uint32_t)b);
-    if (blockIdx.x == 0)
-        for (int k = b; k < FMM_STAT_SLOTS * 16; k += 256) stat[k] = 0;
+    if (blockIdx.x > 0) return;
+    for (int k = b; k < FMM_STAT_SLOTS * 16; k += 256) stat[k] = 0;
+    for (int k = b; k < FMM_WORDS; k += 256) cnt[k] = 0;
+    __syncthreads();
     if (b == 0) {
-        for (int k = 0; k < FMM_LEVELS; k++) cnt[k] = 0;
         cnt[FMM_FRONT] = (uint32_t)nroot;
         cnt[FMM_NODES] = C->node_count;
         for (int l = 0; l <= G4_MAXLEV; l++) cnt[FMM_LEVELS + l] = C->lvl_count[l];
@@ -927,6 +929,13 @@ __global__ __launch_bounds__(256) void k_fmm_particles(FmmArgs A, const uint32_t
 // with the list-based path to round-off but are not bitwise reproducible.
 #define FP_SRC 128  // partner particles in LDS at a time (at 512 fewer wavefronts fit: 2^21 particles 1.4 -> 2.3 ms)
 #define FT_NC 2     // copies of the daughters' field sums in the node-pair passes
+// Pending entries of a wavefront in a node-pair pass (frontier and leaf-node pairs; leaf
+// pairs): written 64 short of these at a time, one atomic each.  Four blocks of 39 KB fit a
+// compute unit.  All passes of 2^21 particles, leaf 16: 3.22 ms with 128 and 256 and the
+// counters in one cache line, 3.10 with a line each; 2.88 with four wavefronts per SIMD for
+// three, then 2.61 with 192 and 384, 2.55 with 192 and 512, 2.83 with 320 and 576 (three blocks).
+#define FT_PAIRS 192
+#define FT_LEAFS 512
 
 __constant__ uint8_t c_tri[36][2] = {{0, 0}, {0, 1}, {1, 1}, {0, 2}, {1, 2}, {2, 2}, {0, 3}, {1, 3}, {2, 3}, {3, 3}, {0, 4}, {1, 4}, {2, 4}, {3, 4}, {4, 4}, {0, 5}, {1, 5}, {2, 5}, {3, 5}, {4, 5}, {5, 5}, {0, 6}, {1, 6}, {2, 6}, {3, 6}, {4, 6}, {5, 6}, {6, 6}, {0, 7}, {1, 7}, {2, 7}, {3, 7}, {4, 7}, {5, 7}, {6, 7}, {7, 7}};  // daughter pairs (i <= j) of a self pair, j-major
 
@@ -999,11 +1008,11 @@ __global__ void k_fast_init(FastArgs A, const DevCounters *__restrict__ C, int n
     if (b >= nroot || (A.wn[b].meta & WN_LEAF)) return;
     const uint32_t o = atomicAdd(&A.cnt[FMM_FRONT], 1u);
     if (o < A.cap_pairs) A.fout[o] = make_uint2((uint32_t)b, (uint32_t)b);
-    else atomicOr(&A.cnt[4], 1u);
+    else atomicOr(&A.cnt[FMM_OVER], 1u);
 }
 
-// Wavefront-local staging of appended pairs: up to 127 pending entries in LDS,
-// written out 64 at a time with one atomic on the global counter.
+// Wavefront-local staging of appended pairs: up to CAP - 1 pending entries in LDS,
+// written out CAP - 64 at a time with one atomic on the global counter.
 template <uint32_t CAP>
 struct Stage {
     uint2 *buf;        // LDS, CAP entries; a push adds at most 64, writes go out CAP - 64 at a time
@@ -1074,27 +1083,29 @@ __device__ __forceinline__ void fm_combine(float f[20], uint32_t take)
     }
 }
 
+// four wavefronts per SIMD (128 VGPRs, 131 without the bound; with the table of the
+// periodic correction it would spill)
 template <bool POT, bool EW>
-__global__ __launch_bounds__(256) void k_fast_open(FastArgs A)
+__global__ __launch_bounds__(256, EW ? 1 : 4) void k_fast_open(FastArgs A)
 {
     // field sums of the daughters, FT_NC copies: the lanes of one daughter spread over the
     // copies, since float atomics to one LDS address serialise
     __shared__ float Floc[4][FT_NC][16][20];
-    __shared__ uint2 sbf[4][128], sbl[4][256], sbn[4][128];  // staging: frontier, leaf pairs, leaf-node pairs
+    __shared__ uint2 sbf[4][FT_PAIRS], sbl[4][FT_LEAFS], sbn[4][FT_PAIRS];  // staging: frontier, leaf pairs, leaf-node pairs
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     float(*FL)[16][20] = Floc[wv];
     for (int v = lane; v < FT_NC * 320; v += 64) (&FL[0][0][0])[v] = 0.f;
     // after an overflow the host retries with more room: decided once per block, since
     // every wavefront of it must reach the barriers at the end
     __shared__ uint32_t s_over, left[3][4], base3[3];
-    if (threadIdx.x == 0) s_over = A.cnt[4];
+    if (threadIdx.x == 0) s_over = A.cnt[FMM_OVER];
     if (blockIdx.x == 0 && threadIdx.x == 0) *A.cnext = 0;
     __syncthreads();
     if (s_over) return;
     const uint32_t nin = min(*A.cin, A.cap_pairs);
     uint32_t c_nn = 0;
-    Stage<128> sf{sbf[wv], 0u}, sn{sbn[wv], 0u};
-    Stage<256> sl{sbl[wv], 0u};
+    Stage<FT_PAIRS> sf{sbf[wv], 0u}, sn{sbn[wv], 0u};
+    Stage<FT_LEAFS> sl{sbl[wv], 0u};
     const uint32_t stride = gridDim.x * 4;
     uint32_t it = blockIdx.x * 4 + wv;
     uint2 pr = it < nin ? A.fin[it] : make_uint2(0u, 0u);
@@ -1269,9 +1280,9 @@ __global__ __launch_bounds__(256) void k_fast_open(FastArgs A)
         st_push(sf, (act == 3 && !l1) || (act == 2 && !l1 && !l2), pij);
         st_push(sl, act == 2 && l1 && l2, pij);
         st_push(sn, act == 2 && (l1 != l2), l1 ? pij : make_uint2(cb + j, ca + i));
-        st_flush(sf, A.fout, A.cout, A.cap_pairs, &A.cnt[4]);
-        st_flush(sl, A.ll, &A.cnt[2], A.cap_ll, &A.cnt[4]);
-        st_flush(sn, A.ln, &A.cnt[3], A.cap_ln, &A.cnt[4]);
+        st_flush(sf, A.fout, A.cout, A.cap_pairs, &A.cnt[FMM_OVER]);
+        st_flush(sl, A.ll, &A.cnt[FMM_LIST0], A.cap_ll, &A.cnt[FMM_OVER]);
+        st_flush(sn, A.ln, &A.cnt[FMM_LIST1], A.cap_ln, &A.cnt[FMM_OVER]);
     }
     // the rest of the block's four wavefronts, with one atomic per list
     if (lane == 0) {
@@ -1282,7 +1293,7 @@ __global__ __launch_bounds__(256) void k_fast_open(FastArgs A)
     __syncthreads();
     if (threadIdx.x < 3) {
         const uint32_t *n = left[threadIdx.x], sum = n[0] + n[1] + n[2] + n[3];
-        base3[threadIdx.x] = sum ? atomicAdd(threadIdx.x == 0 ? A.cout : &A.cnt[1 + threadIdx.x], sum) : 0u;
+        base3[threadIdx.x] = sum ? atomicAdd(threadIdx.x == 0 ? A.cout : &A.cnt[threadIdx.x == 1 ? FMM_LIST0 : FMM_LIST1], sum) : 0u;
     }
     __syncthreads();
     uint32_t at[3];
@@ -1291,9 +1302,9 @@ __global__ __launch_bounds__(256) void k_fast_open(FastArgs A)
         at[k] = base3[k];
         for (int w = 0; w < wv; w++) at[k] += left[k][w];
     }
-    st_put(sf, A.fout, at[0], A.cap_pairs, &A.cnt[4]);
-    st_put(sl, A.ll, at[1], A.cap_ll, &A.cnt[4]);
-    st_put(sn, A.ln, at[2], A.cap_ln, &A.cnt[4]);
+    st_put(sf, A.fout, at[0], A.cap_pairs, &A.cnt[FMM_OVER]);
+    st_put(sl, A.ll, at[1], A.cap_ll, &A.cnt[FMM_OVER]);
+    st_put(sn, A.ln, at[2], A.cap_ln, &A.cnt[FMM_OVER]);
     fmm_count(A.stat, 0, 0, lane == 0 ? c_nn : 0u);
 }
 
@@ -2031,9 +2042,9 @@ static void launch_fast_particles(const FastArgs &A, uint32_t nnodes, uint32_t n
 template <typename Args>
 static void fmm_turn(Args &A, int pass)
 {
-    A.cin = A.cnt + FMM_FRONT + pass % 3;
-    A.cout = A.cnt + FMM_FRONT + (pass + 1) % 3;
-    A.cnext = A.cnt + FMM_FRONT + (pass + 2) % 3;
+    A.cin = A.cnt + FMM_FRONT + pass % 3 * 32;
+    A.cout = A.cnt + FMM_FRONT + (pass + 1) % 3 * 32;
+    A.cnext = A.cnt + FMM_FRONT + (pass + 2) % 3 * 32;
 }
 
 static int fmm_fast(g4_ctx *ctx, g4_tree *t, const g4_fmm_params *fp, double factor, void *ws, size_t ws_bytes,
@@ -2109,14 +2120,14 @@ static int fmm_fast(g4_ctx *ctx, g4_tree *t, const g4_fmm_params *fp, double fac
             G4_HIP(ctx, hipGetLastError());
             G4_HIP(ctx, hipMemcpyAsync(hc, A.cnt, sizeof(hc), hipMemcpyDeviceToHost, s));
             G4_HIP(ctx, hipStreamSynchronize(s));
-            if (hc[4]) return g4_set_err(ctx, G4_ENOMEM, "fmm lists exceed the workspace");
-            done = hc[FMM_FRONT + (pass + 1) % 3] == 0;
+            if (hc[FMM_OVER]) return g4_set_err(ctx, G4_ENOMEM, "fmm lists exceed the workspace");
+            done = hc[FMM_FRONT + (pass + 1) % 3 * 32] == 0;
         }
     }
     if (!done) return g4_set_err(ctx, G4_EHIP, "fmm dual walk did not terminate");
     const uint32_t nnodes = hc[FMM_NODES], *levels = hc + FMM_LEVELS;
     if (nnodes < 1 || (int64_t)nnodes > t->cap) return g4_set_err(ctx, G4_EHIP, "bad node count");
-    const uint32_t nll = hc[2], nln = hc[3];
+    const uint32_t nll = hc[FMM_LIST0], nln = hc[FMM_LIST1];
     // 2. partner lists of the leaf pairs (counting sort by leaf), then all particle pairs per leaf
     uint32_t *cursor = (uint32_t *)(b + L.cursor), *bsum = (uint32_t *)(b + L.bsum);
     if (int zst = g4_launch_zero(ctx, A.pstart, (size_t)(nnodes + 1) * 4)) return zst;
@@ -2234,12 +2245,12 @@ int g4_launch_fmm(g4_ctx *ctx, g4_tree *t, const g4_fmm_params *fp, double facto
             G4_HIP(ctx, hipGetLastError());
             G4_HIP(ctx, hipMemcpyAsync(hc, A.cnt, sizeof(hc), hipMemcpyDeviceToHost, s));
             G4_HIP(ctx, hipStreamSynchronize(s));
-            if (hc[4]) return g4_set_err(ctx, G4_ENOMEM, "fmm interaction lists exceed the workspace");
-            done = hc[FMM_FRONT + (pass + 1) % 3] == 0;
+            if (hc[FMM_OVER]) return g4_set_err(ctx, G4_ENOMEM, "fmm interaction lists exceed the workspace");
+            done = hc[FMM_FRONT + (pass + 1) % 3 * 32] == 0;
         }
     }
     if (!done) return g4_set_err(ctx, G4_EHIP, "fmm dual walk did not terminate");
-    const uint32_t n_node = hc[2], n_part = hc[3], *levels = hc + FMM_LEVELS;
+    const uint32_t n_node = hc[FMM_LIST0], n_part = hc[FMM_LIST1], *levels = hc + FMM_LEVELS;
     const int64_t nn_host = hc[FMM_NODES];
     // sort the entries by (target, source): each target's sum then runs in source order,
     // independent of the order in which the walk appended its entries
