@@ -48,8 +48,9 @@ def check_links(ex, n, nroot=1):
     (1, 1, 21, 0), (2, 1, 21, 0), (8, 8, 21, 0), (9, 8, 21, 0), (1023, 8, 21, 0), (1024, 1, 21, 1), (1025, 32, 21, 0),
     (4099, 1, 21, 0), (4099, 16, 21, 1), (4099, 5, 1, 0), (4099, 5, 3, 1), (5000, 1023, 21, 0), (5000, 1024, 21, 0),
     (5000, 1025, 21, 0), (9001, 3000, 21, 1), (3000, 3000, 21, 0), (3001, 3000, 21, 0), (200003, 24, 21, 0),
-    # the sort's small form: tiles of 512 keys, up to 128 of them
-    (511, 4, 21, 0), (513, 4, 21, 1), (65536, 8, 21, 0), (65537, 8, 21, 1)])
+    # the sort's small forms: up to 128 tiles of 1024 keys, then of 2048
+    (511, 4, 21, 0), (513, 4, 21, 1), (65536, 8, 21, 0), (65537, 8, 21, 1), (131072, 24, 21, 0), (131073, 24, 21, 1),
+    (262144, 32, 21, 1), (262145, 32, 21, 0)])
 @pytest.mark.parametrize("periodic", [True, False])
 def test_nodes_match_oracle(g, n, B, maxd, keys, periodic):
     ctx = g.Context()
