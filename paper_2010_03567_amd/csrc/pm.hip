@@ -415,17 +415,17 @@ __global__ void k_pm_interp(const uint4 *__restrict__ parts, const uint32_t *__r
 // ------------------------------------------------------------------- tiles
 // A cube of PM_CUBE^3 mesh cells is a node of the curve, so its particles are one
 // run of the sorted ones.  With enough particles per cube the mesh around a cube
-// is staged in LDS: the deposit adds there and writes each cell once (cells that
-// no other cube's particles reach are stored, the others added), where the
-// 8 float atomics per particle to memory were the bound; the interpolation
+// is staged in LDS: the deposit adds there and then once per cell to memory, where
+// the 8 float atomics per particle were the bound; the interpolation
 // reads its 56 potentials per particle from LDS instead of through L1.
 //
 // The rule: at least PM_TILE_MIN particles per cube on average, which pay for
-// staging its 4913 and 9261 mesh points, and PM_TILE_N in all, which pay for the
-// work list.  Whole call by memory / by tiles, ms: 2e5 particles at 128^3 (391 a
-// cube) 0.125 / 0.115, at 64^3 (3125) 0.066 / 0.081, at 256^3 (49) 0.262 / 0.274;
-// 10^6 at 64^3 0.138 / 0.125, at 256^3 (244) 0.433 / 0.340; 4e6 at 512^3 (122)
-// 2.86 / 2.68; 2^24 at 512^3 (512) 6.07 / 4.21.
+// staging its 4913 and 9261 mesh points, and PM_TILE_N in all (a third of it from 128^3
+// on, where the mesh fills the chip's blocks with cubes), which pay for the work
+// list.  Whole call by memory / by tiles, ms: 2e5 particles at 128^3 (391 a cube)
+// 0.125 / 0.103, at 64^3 (3125) 0.066 / 0.071, at 256^3 (49) 0.262 / 0.257; 10^6 at
+// 64^3 0.139 / 0.122, at 256^3 (244) 0.433 / 0.305; 4e6 at 512^3 (122) 2.84 / 2.18; 2^24
+// at 512^3 (512) 6.03 / 2.95.
 #define PM_TILE_MIN 100
 #define PM_TILE_N 500000
 #define PM_CUBE_BITS 4
@@ -448,7 +448,7 @@ __global__ void k_pm_starts(const uint64_t *__restrict__ keys, int64_t n, int ks
     for (uint32_t c = lo; c <= hi; c++) start[c] = (uint32_t)i;
 }
 
-// work items (first particle, count, 1 if the cube has no other item)
+// work items (first particle, count)
 __global__ __launch_bounds__(256) void k_pm_items(const uint32_t *__restrict__ start, uint32_t ncube,
                                                   uint4 *__restrict__ items, uint32_t *__restrict__ nitems)
 {
@@ -465,7 +465,7 @@ __global__ __launch_bounds__(256) void k_pm_items(const uint32_t *__restrict__ s
     if (lane == 63 && incl) base = atomicAdd(nitems, incl);
     base = (uint32_t)__shfl((int)base, 63) + incl - parts;
     for (uint32_t k = 0; k < parts; k++)
-        items[base + k] = make_uint4(first + k * PM_ITEM, min(count - k * PM_ITEM, (uint32_t)PM_ITEM), parts == 1, 0u);
+        items[base + k] = make_uint4(first + k * PM_ITEM, min(count - k * PM_ITEM, (uint32_t)PM_ITEM), 0u, 0u);
 }
 
 // A thread takes a run of consecutive particles: particles of one cell follow
@@ -520,16 +520,20 @@ __global__ __launch_bounds__(PM_DEP_THREADS) void k_pm_deposit_tile(const uint4 
     if (cell >= 0) flush();
     __syncthreads();
     const int mask = ng - 1;
-    for (int e = threadIdx.x; e < PM_DT * PM_DT * PM_DT; e += PM_DEP_THREADS) {
-        const float v = tile[e];
-        const int x = e / (PM_DT * PM_DT), y = e / PM_DT % PM_DT, z = e % PM_DT;
-        if (v == 0.f) continue;
-        float *o = &mesh[((size_t)((bx + x) & mask) << (2 * lg)) + ((size_t)((by + y) & mask) << lg) +
-                         (size_t)((bz + z) & mask)];
-        const bool own = x > 0 && x < PM_CUBE && y > 0 && y < PM_CUBE && z > 0 && z < PM_CUBE;
-        if (it.z && own) *o = v;
-        else atomicAdd(o, v);
-    }
+    // 16 lanes add a row of the cube, one line of memory, then the points above the rows
+    // follow.  (Points that no other cube reaches need no atomic, but storing those and adding
+    // only the cube's shell broke every row into three requests: mesh 512^3, 2^24 particles
+    // 1.02 ms with the stores, 0.62 all atomic, 0.58 row by row.)
+    auto add = [&](int row, int z) {
+        const float v = tile[row * PM_DT + z];
+        const int x = row / PM_DT, y = row - x * PM_DT;
+        if (v != 0.f)
+            atomicAdd(&mesh[((size_t)((bx + x) & mask) << (2 * lg)) + ((size_t)((by + y) & mask) << lg) +
+                            (size_t)((bz + z) & mask)], v);
+    };
+    for (int row = threadIdx.x / PM_CUBE; row < PM_DT * PM_DT; row += PM_DEP_THREADS / PM_CUBE)
+        add(row, threadIdx.x % PM_CUBE);
+    for (int row = threadIdx.x; row < PM_DT * PM_DT; row += PM_DEP_THREADS) add(row, PM_CUBE);
 }
 
 __global__ __launch_bounds__(PM_INT_THREADS) void k_pm_interp_tile(const uint4 *__restrict__ parts,
@@ -548,6 +552,8 @@ __global__ __launch_bounds__(PM_INT_THREADS) void k_pm_interp_tile(const uint4 *
               by = ((int)(q0.y >> shift) & ~(PM_CUBE - 1)) - 2,
               bz = ((int)(q0.z >> shift) & ~(PM_CUBE - 1)) - 2;
     const int mask = ng - 1;
+    // several loads in flight (512^3, 2^24 particles: 1.01 ms one by one, 0.85 by 2, 0.83 by 6, 0.90 by 10)
+#pragma unroll 6
     for (int e = threadIdx.x; e < PM_IT * PM_IT * PM_IT; e += PM_INT_THREADS) {
         const int x = e / (PM_IT * PM_IT), y = e / PM_IT % PM_IT, z = e % PM_IT;
         tile[e] = phi[((size_t)((bx + x) & mask) << (2 * lg)) + ((size_t)((by + y) & mask) << lg) +
@@ -624,7 +630,7 @@ int g4_launch_pm(g4_ctx *ctx, const g4_tree *t, const g4_pm_params *pp, void *ws
     const size_t max_items = ncube + (size_t)(n / PM_ITEM);
     uint32_t *nitems = (uint32_t *)(b + L.spare), *start = nitems + 64;
     uint4 *items = (uint4 *)(b + L.spare + 256 + ((size_t)ncube + 1 + 63) / 64 * 256);
-    const bool tiles = ncube && n >= (int64_t)PM_TILE_MIN * ncube && n >= PM_TILE_N &&
+    const bool tiles = ncube && n >= (int64_t)PM_TILE_MIN * ncube && n >= (ng >= 128 ? PM_TILE_N / 3 : PM_TILE_N) &&
                        (char *)(items + max_items) <= b + L.total;
     if (tiles) {
         k_pm_starts<<<(unsigned)((n + 1 + 255) / 256), 256, 0, s>>>(t->keys1, n, 3 * (G4_MAXLEV - lg + PM_CUBE_BITS), ncube,

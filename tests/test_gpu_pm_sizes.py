@@ -59,9 +59,10 @@ def reference(X, mass, ng, box, r_s, G):
 
 @pytest.mark.parametrize("ng,n,keys", [(8, 1, 0), (8, 300, 0), (16, 3001, 0), (32, 777, 1), (64, 3001, 0), (128, 3001, 0),
                                        (256, 20011, 0), (512, 20011, 1), (1024, 3001, 0), (32, 70001, 0), (64, 500009, 1),
-                                       # tiles (from 5e5 particles and 100 per 16^3 cells): one cube, staged or not, several items a cube
+                                       # tiles (from 5e5 particles, a third of that from 128^3 on, and 100 per
+                                       # 16^3 cells): one cube, staged or not, several items a cube
                                        (16, 500000, 0), (32, 500003, 1), (128, 500003, 0), (256, 600011, 1),
-                                       (128, 1300003, 0), (256, 409600, 0)])
+                                       (128, 166665, 0), (128, 166666, 1), (128, 1300003, 0), (256, 409600, 0)])
 def test_pm_sizes(g, ng, n, keys):
     ctx = g.Context()
     box, G = 2.5, 0.7
