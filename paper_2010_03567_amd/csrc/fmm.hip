@@ -78,7 +78,8 @@ struct FmmArgs {
     uint32_t *cnt;   // [2] node entries, [3] particle entries, [4] overflow (FMM_* below)
     uint32_t *cin, *cout, *cnext;  // this pass's and the next one's frontier sizes; the one after, cleared
     uint32_t cap_pairs;
-    // entries: key = target << 32 | order key of the source, value = source (type bits | index)
+    // entries: key = target << kshift | order key of the source, value = source (type bits | index)
+    int kshift;
     uint64_t *nkey;
     uint32_t *nval;
     uint32_t cap_node;
@@ -281,7 +282,7 @@ __device__ __forceinline__ uint32_t src_order(const FmmArgs &A, uint32_t src)
 __device__ __forceinline__ void put(uint64_t *key, uint32_t *val, uint32_t at, const FmmArgs &A, uint32_t target,
                                     uint32_t src)
 {
-    key[at] = ((uint64_t)target << 32) | src_order(A, src);
+    key[at] = ((uint64_t)target << A.kshift) | src_order(A, src);
     val[at] = src;
 }
 
@@ -446,13 +447,13 @@ __global__ void k_fmm_init(uint32_t *cnt, uint2 *f0, unsigned long long *stat, c
 }
 
 // ------------------------------------------------------------ CSR of entries
-__global__ void k_fmm_csr(const uint64_t *__restrict__ key, uint32_t n, uint32_t *__restrict__ start,
+__global__ void k_fmm_csr(const uint64_t *__restrict__ key, int kshift, uint32_t n, uint32_t *__restrict__ start,
                           uint32_t *__restrict__ end)
 {
     for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
-        const uint32_t k = (uint32_t)(key[i] >> 32);
-        if (i == 0 || (uint32_t)(key[i - 1] >> 32) != k) start[k] = i;
-        if (i == n - 1 || (uint32_t)(key[i + 1] >> 32) != k) end[k] = i + 1;
+        const uint32_t k = (uint32_t)(key[i] >> kshift);
+        if (i == 0 || (uint32_t)(key[i - 1] >> kshift) != k) start[k] = i;
+        if (i == n - 1 || (uint32_t)(key[i + 1] >> kshift) != k) end[k] = i + 1;
     }
 }
 
@@ -2228,6 +2229,9 @@ int g4_launch_fmm(g4_ctx *ctx, g4_tree *t, const g4_fmm_params *fp, double facto
     A.pval = (uint32_t *)(b + L.pval);
     A.cap_part = L.cap_part;
     A.bfirst = t->bfirst;
+    // the target right above the source's order key, so that the sort has no pass over zeros
+    // between them (30 k particles: 5 passes a list for 6)
+    A.kshift = std::min(32, bits_for((uint64_t)t->n) + 5);
     A.stat = (unsigned long long *)(A.cnt + FMM_STATS);
     uint2 *fr[2] = {(uint2 *)(b + L.f0), (uint2 *)(b + L.f1)};
     if ((uint64_t)t->nbox > L.cap_pairs) return g4_set_err(ctx, G4_ENOMEM, "fmm frontier smaller than the root count");
@@ -2258,8 +2262,8 @@ int g4_launch_fmm(g4_ctx *ctx, g4_tree *t, const g4_fmm_params *fp, double facto
     uint32_t *nv2 = (uint32_t *)(b + L.nval2), *pv2 = (uint32_t *)(b + L.pval2);
     int alt = 0;
     if (n_node) {
-        if (int st = g4_radix_sort_u64(ctx, A.nkey, nk2, A.nval, nv2, n_node, 0, 32 + bits_for((uint64_t)nn_host),
-                                       b + L.sort_tmp, L.sort_bytes, &alt))
+        if (int st = g4_radix_sort_u64(ctx, A.nkey, nk2, A.nval, nv2, n_node, 0,
+                                       A.kshift + bits_for((uint64_t)nn_host), b + L.sort_tmp, L.sort_bytes, &alt))
             return st;
         if (!alt) {
             std::swap(A.nkey, nk2);
@@ -2267,8 +2271,8 @@ int g4_launch_fmm(g4_ctx *ctx, g4_tree *t, const g4_fmm_params *fp, double facto
         }
     }
     if (n_part) {
-        if (int st = g4_radix_sort_u64(ctx, A.pkey, pk2, A.pval, pv2, n_part, 0, 32 + bits_for((uint64_t)t->n),
-                                       b + L.sort_tmp, L.sort_bytes, &alt))
+        if (int st = g4_radix_sort_u64(ctx, A.pkey, pk2, A.pval, pv2, n_part, 0,
+                                       A.kshift + bits_for((uint64_t)t->n), b + L.sort_tmp, L.sort_bytes, &alt))
             return st;
         if (!alt) {
             std::swap(A.pkey, pk2);
@@ -2282,8 +2286,8 @@ int g4_launch_fmm(g4_ctx *ctx, g4_tree *t, const g4_fmm_params *fp, double facto
     if (int zst = g4_launch_zero(ctx, nend, (size_t)t->cap * 4)) return zst;
     if (int zst = g4_launch_zero(ctx, pstart, (size_t)t->n * 4)) return zst;
     if (int zst = g4_launch_zero(ctx, pend, (size_t)t->n * 4)) return zst;
-    if (n_node) k_fmm_csr<<<2048, 256, 0, s>>>(nk2, n_node, nstart, nend);
-    if (n_part) k_fmm_csr<<<2048, 256, 0, s>>>(pk2, n_part, pstart, pend);
+    if (n_node) k_fmm_csr<<<2048, 256, 0, s>>>(nk2, A.kshift, n_node, nstart, nend);
+    if (n_part) k_fmm_csr<<<2048, 256, 0, s>>>(pk2, A.kshift, n_part, pstart, pend);
     A.nval = nv2;
     A.pval = pv2;
     float *F = (float *)(b + L.F);
