@@ -31,6 +31,7 @@ __host__ __device__ constexpr int ew_idx(int a, int b, int c)
 // of the offset.
 struct EwPoint {
     const float *row;
+    uint32_t point;  // index of the grid point
     float m[20];
     float sx, sy, sz;
 };
@@ -47,7 +48,8 @@ __device__ __forceinline__ EwPoint ew_locate(const float *__restrict__ tab, int 
     const int j = min((int)fmaf(uy, hinv, 0.5f), ne);
     const int k = min((int)fmaf(uz, hinv, 0.5f), ne);
     const float ex = fmaf(-(float)i, h, ux), ey = fmaf(-(float)j, h, uy), ez = fmaf(-(float)k, h, uz);
-    p.row = tab + ((size_t)(i * (ne + 1) + j) * (ne + 1) + k) * G4_EWALD_NCOMP;
+    p.point = (uint32_t)((i * (ne + 1) + j) * (ne + 1) + k);
+    p.row = tab + (size_t)p.point * G4_EWALD_NCOMP;
     const float xx = ex * ex, yy = ey * ey, zz = ez * ez;
     float *m = p.m;
     m[ew_idx(0, 0, 0)] = 1.f;
@@ -73,21 +75,82 @@ __device__ __forceinline__ EwPoint ew_locate(const float *__restrict__ tab, int 
     return p;
 }
 
-// D^(A,B,C) psi at the located point (octant frame): sum_{|b| <= 3} D^(A,B,C)+b (x0) m_b
-template <int A, int B, int C>
-__device__ __forceinline__ float ew_taylor(const EwPoint &p)
+// exponent of axis k in the component `idx` (of order <= 3)
+__host__ __device__ constexpr int ew_exponent(int idx, int k)
 {
-    float s = 0.f;
+    for (int o = 0; o <= 3; o++)
+        for (int a = o; a >= 0; a--)
+            for (int b = o - a; b >= 0; b--)
+                if (ew_idx(a, b, o - a - b) == idx) return k == 0 ? a : (k == 1 ? b : o - a - b);
+    return 0;
+}
+
+// D^(A,B,C) psi at the located point (octant frame): sum_{|b| <= 3} D^(A,B,C)+b (x0) m_b, the
+// highest order first.  Written out at compile time, so that a row in registers stays there.
+template <int A, int B, int C, int N = 0>
+__device__ __forceinline__ float ew_taylor(const EwPoint &p, float s = 0.f)
+{
+    if constexpr (N < 20) {
+        constexpr int b = N < 10 ? 10 + N : (N < 16 ? N - 6 : (N < 19 ? N - 15 : 0));
+        constexpr int at = ew_idx(A + ew_exponent(b, 0), B + ew_exponent(b, 1), C + ew_exponent(b, 2));
+        return ew_taylor<A, B, C, N + 1>(p, fmaf(p.row[at], p.m[b], s));
+    } else {
+        return s;
+    }
+}
+
+typedef float ew_f4 __attribute__((ext_vector_type(4)));
+
+// This lane's row, fetched by the wavefront together (all 64 lanes call it): four lanes
+// read 64 contiguous bytes of one row, and `buf` (256 vectors of LDS, the wavefront's own)
+// turns them over to the row's lane.  With every lane reading its own row a load instruction
+// touched 42 cache lines, and the walk at p = 3 was bound by that (texture data units busy
+// 74 % of the time, VALU 35 %): tree and walks of 48^3 particles 4.72 -> 4.08 ms, of 20 k
+// 1.40 -> 1.15.  Where nine vectors of a row are enough (particle pairs, nodes at p = 2)
+// the lanes share more lines and reading them alone is faster (p = 2, 110 k particles:
+// 3.7 ms alone, 4.3 together).
+__device__ __forceinline__ void ew_fetch(const float *__restrict__ tab, uint32_t point, ew_f4 *buf,
+                                         float (&r)[G4_EWALD_NCOMP])
+{
+    constexpr int N = G4_EWALD_NCOMP / 4, G = N / 4;
+    const int lane = threadIdx.x & 63;
+    const ew_f4 *t4 = reinterpret_cast<const ew_f4 *>(tab);
+    const ew_f4 *src[4];
 #pragma unroll
-    for (int o = 3; o >= 0; o--)
+    for (int u = 0; u < 4; u++)
+        src[u] = t4 + (size_t)(uint32_t)__shfl((int)point, 16 * u + (lane >> 2)) * N + (lane & 3);
+    ew_f4 v[G][4];
 #pragma unroll
-        for (int b1 = o; b1 >= 0; b1--)
+    for (int g = 0; g < G; g++)
 #pragma unroll
-            for (int b2 = o - b1; b2 >= 0; b2--) {
-                const int b3 = o - b1 - b2;
-                s = fmaf(p.row[ew_idx(A + b1, B + b2, C + b3)], p.m[ew_idx(b1, b2, b3)], s);
-            }
-    return s;
+        for (int u = 0; u < 4; u++) v[g][u] = src[u][4 * g];
+    // of the last, incomplete group of four every lane reads its own
+#pragma unroll
+    for (int k = 4 * G; k < N; k++) {
+        const ew_f4 x = t4[(size_t)point * N + k];
+        r[4 * k] = x.x;
+        r[4 * k + 1] = x.y;
+        r[4 * k + 2] = x.z;
+        r[4 * k + 3] = x.w;
+    }
+#pragma unroll
+    for (int g = 0; g < G; g++) {
+        // the quarters of a row in an order that depends on the row: no bank conflicts either way
+#pragma unroll
+        for (int u = 0; u < 4; u++) buf[64 * u + (lane >> 2) * 4 + ((lane & 3) ^ (lane >> 3 & 3))] = v[g][u];
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int k = 0; k < 4; k++) {
+            const ew_f4 x = buf[4 * lane + (k ^ (lane >> 1 & 3))];
+            r[16 * g + 4 * k] = x.x;
+            r[16 * g + 4 * k + 1] = x.y;
+            r[16 * g + 4 * k + 2] = x.z;
+            r[16 * g + 4 * k + 3] = x.w;
+        }
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+    }
 }
 
 // grad psi(d) (and psi(d) with POT) for a single source at offset d
@@ -104,23 +167,21 @@ __device__ __forceinline__ void ew_grad(const float *__restrict__ tab, int ne, f
 
 // Correction of a node with mass M, second moments q (xx xy xz yy yz zz) and,
 // for the potential, third moments o (xxx xxy xxz xyy xyz xzz yyy yyz yzz zzz)
-// about its centre of mass at offset d from the target:
+// about its centre of mass at the located offset d from the target:
 //   force  f = M grad psi + (1/2) Q2 : grad^3 psi       (ORD3; M grad psi otherwise)
 //   potential  M psi + (1/2) Q2 : grad^2 psi (+ (1/6) Q3 . grad^3 psi with ORD3)
 // (the node terms of eq. eqnpo1 with the multipole expansion of psi).
 template <bool POT, bool ORD3>
-__device__ __forceinline__ void ew_node(const float *__restrict__ tab, int ne, float h, float hinv, float dx, float dy,
-                                        float dz, float M, float4 qa, float2 qb, const float *__restrict__ o,
-                                        float &fx, float &fy, float &fz, float &fp)
+__device__ __forceinline__ void ew_node_at(const EwPoint &p, float M, float4 qa, float2 qb, const float *__restrict__ o,
+                                           float &fx, float &fy, float &fz, float &fp)
 {
-    const EwPoint p = ew_locate(tab, ne, h, hinv, dx, dy, dz);
     const float sx = p.sx, sy = p.sy, sz = p.sz;
     // moments reflected into the octant frame
     const float qxx = qa.x, qxy = sx * sy * qa.y, qxz = sx * sz * qa.z, qyy = qa.w, qyz = sy * sz * qb.x, qzz = qb.y;
     float gx = M * ew_taylor<1, 0, 0>(p), gy = M * ew_taylor<0, 1, 0>(p), gz = M * ew_taylor<0, 0, 1>(p);
     float t300 = 0.f, t210 = 0.f, t201 = 0.f, t120 = 0.f, t111 = 0.f, t102 = 0.f, t030 = 0.f, t021 = 0.f, t012 = 0.f,
           t003 = 0.f;
-    if (ORD3 || POT) {
+    if (ORD3) {
         t300 = ew_taylor<3, 0, 0>(p);
         t210 = ew_taylor<2, 1, 0>(p);
         t201 = ew_taylor<2, 0, 1>(p);

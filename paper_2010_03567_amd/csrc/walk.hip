@@ -382,10 +382,14 @@ __device__ __forceinline__ uint32_t group_decision(const WalkArgs &A, const WNod
 
 // 64 particle-node interactions from the node ring, one per lane (lanes >= n idle).
 template <int KER, bool POT, bool ORD3, int HI = 0>
-__device__ __forceinline__ void eval_p2m(const WalkArgs &A, WaveLds<POT> &W, uint32_t head, uint32_t n, int lane)
+__device__ __forceinline__ void eval_p2m(const WalkArgs &A, WaveLds<POT> &W, uint32_t head, uint32_t n, int lane,
+                                         ew_f4 *ewbuf)
 {
-    if ((uint32_t)lane >= n) return;
-    const uint32_t q = (head + lane) & (WK_RING - 1);
+    // kernel 3 at p = 3: all lanes fetch the table together, the idle ones repeat the first pair
+    constexpr bool FETCH = KER == 3 && ORD3;
+    const bool on = (uint32_t)lane < n;
+    if (!FETCH && !on) return;
+    const uint32_t q = (head + (FETCH && !on ? 0 : lane)) & (WK_RING - 1);
     const uint32_t node = W.pm_idx[q], t = W.pm_tgt[q];
     const uint4 T = W.tgt[t];
     const WNode *nd = A.wn + node;
@@ -440,12 +444,19 @@ __device__ __forceinline__ void eval_p2m(const WalkArgs &A, WaveLds<POT> &W, uin
     if constexpr (KER == 3) {
         // the other images: g = 1/r - psi, so the node adds +f (force) and +phi_psi (potential)
         float cx, cy, cz, cp = 0.f;
-        ew_node<POT, ORD3>(A.ew, A.ew_n, A.ew_h, A.ew_hinv, dx, dy, dz, mass, qa, qb, A.q3 + (size_t)node * 10, cx, cy,
-                           cz, cp);
+        EwPoint p = ew_locate(A.ew, A.ew_n, A.ew_h, A.ew_hinv, dx, dy, dz);
+        float row[ORD3 ? G4_EWALD_NCOMP : 1];
+        if constexpr (ORD3) {
+            // the quadrupole force takes psi's derivatives to order 6, the whole row
+            ew_fetch(A.ew, p.point, ewbuf, row);
+            p.row = row;
+        }
+        ew_node_at<POT, ORD3>(p, mass, qa, qb, A.q3 + (size_t)node * 10, cx, cy, cz, cp);
         fx -= cx;
         fy -= cy;
         fz -= cz;
         if (POT) fp -= cp;
+        if (FETCH && !on) return;
     }
     lds_add(&W.acc[0][t], -(double)fx);
     lds_add(&W.acc[1][t], -(double)fy);
@@ -455,9 +466,11 @@ __device__ __forceinline__ void eval_p2m(const WalkArgs &A, WaveLds<POT> &W, uin
 
 // Wavefronts per SIMD the register budget must allow: the LDS of the walks
 // without the potential leaves room for 7, which the Newtonian and TreePM
-// kernels at p <= 3 reach within 72 VGPRs without spilling; the others keep
-// the compiler's own choice.
-#define WALK_MIN_WAVES(KER, POT, HI) ((!(POT) && (KER) <= 1 && (HI) == 0) ? 7 : 1)
+// kernels at p <= 3 reach within 72 VGPRs without spilling.  The periodic
+// Newtonian walk holds a table row of 84 values and gets 3 (168 VGPRs, a few
+// spilled; 48^3 particles 4.08 ms, 4.43 with two wavefronts, 6.6 with four).
+// The others keep the compiler's own choice.
+#define WALK_MIN_WAVES(KER, POT, HI) ((POT) || (HI) || (KER) == 2 ? 1 : (KER) <= 1 ? 7 : 3)
 
 // ORD3: p = 3, the force includes the quadrupole term (p = 2: monopole force);
 // HI = 4 or 5: the orders above (ORD3 set as well)
@@ -467,6 +480,9 @@ __global__ __launch_bounds__(256, WALK_MIN_WAVES(KER, POT, HI)) void k_walk(cons
     __shared__ WaveLds<POT> lds[4];
     const int lane = threadIdx.x & 63;
     WaveLds<POT> &W = lds[threadIdx.x >> 6];
+    constexpr bool FETCH = KER == 3 && ORD3;
+    __shared__ ew_f4 ewlds[FETCH ? 4 : 1][FETCH ? 256 : 1];  // table rows under way (ew_fetch)
+    ew_f4 *const ewb = ewlds[FETCH ? threadIdx.x >> 6 : 0];
     uint4 *const spill = A.spill + (size_t)(blockIdx.x * 4 + (threadIdx.x >> 6)) * WK_SPILL;
     uint32_t t_pp = 0;                                 // per-lane total of particle-particle pairs
     uint32_t u_pm = 0, u_visit = 0;                    // wavefront totals (per launch < 2^32 per wave)
@@ -794,7 +810,7 @@ __global__ __launch_bounds__(256, WALK_MIN_WAVES(KER, POT, HI)) void k_walk(cons
           }
             if (pm_t - pm_h >= 64) {
                 wave_sync_lds();
-                eval_p2m<KER, POT, ORD3, HI>(A, W, pm_h, 64u, lane);
+                eval_p2m<KER, POT, ORD3, HI>(A, W, pm_h, 64u, lane, ewb);
                 pm_h += 64;
                 w_pm++;
             }
@@ -842,7 +858,7 @@ __global__ __launch_bounds__(256, WALK_MIN_WAVES(KER, POT, HI)) void k_walk(cons
     wave_sync_lds();
     while (pm_t != pm_h) {
         const uint32_t n = min(pm_t - pm_h, 64u);
-        eval_p2m<KER, POT, ORD3, HI>(A, W, pm_h, n, lane);
+        eval_p2m<KER, POT, ORD3, HI>(A, W, pm_h, n, lane, ewb);
         pm_h += n;
         w_pm++;
     }
