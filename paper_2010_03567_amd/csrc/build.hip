@@ -700,12 +700,13 @@ __global__ __launch_bounds__(512) void k_moments_block(const DevCounters *__rest
 }
 
 // Levels 0 to MOM_TOP hold at most 73 nodes (per box) and the levels from
-// MOM_DEEP on of a small set few or none: one block takes each of these ranges, a
-// launch instead of one per level (2 to 8 us each).  Moments of 8192 particles, leaf
-// 8: 0.10 -> 0.08 ms.
+// MOM_DEEP on of a small set few or none, also where the set is the dense core of a
+// larger one: one block takes each of these ranges, a launch instead of one per level.
+// 8192 Plummer particles, leaf 16, 90 us (83 with the block from level 13 on); the same
+// in a fiftieth of the space, 10 k of them 108 us and 30 k 118 (180 and 404 from level 13 on).
 #define MOM_TOP 2
-#define MOM_DEEP 13
-#define MOM_DEEP_N 65536  // a denser set may have many nodes that deep
+#define MOM_DEEP 17
+#define MOM_DEEP_N 16384  // a denser set may have many nodes that deep
 
 int g4_launch_moments(g4_ctx *ctx, g4_tree *t)
 {
