@@ -66,38 +66,59 @@ __device__ __forceinline__ void pm_cell(uint32_t X, int shift, float wscale, int
 // in consecutive lanes (the cell index is a prefix of the curve key; each CIC
 // corner is the same shift of it).  Every corner's contributions are summed
 // over such runs by a segmented scan across the wavefront and the last lane
-// of a run issues the one atomic: in haloes most atomics disappear.
+// of a run issues the one atomic: in haloes most atomics disappear.  A wavefront
+// takes PM_RUN times 64 consecutive particles and carries the run at the end of each 64
+// over to the next, which also leaves fewer sums to the order of the atomics.
+#define PM_RUN 4
 __global__ void k_pm_deposit(const uint4 *__restrict__ parts, int64_t n, int ng, int shift, float wscale,
                              float *__restrict__ mesh)
 {
     const int lane = threadIdx.x & 63;
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t base = blockIdx.x * (int64_t)blockDim.x; base < n; base += stride) {
-        const int64_t p = base + threadIdx.x;
-        const bool act = p < n;
-        const uint4 q = act ? parts[p] : make_uint4(0u, 0u, 0u, 0u);
-        const float m = act ? __uint_as_float(q.w) : 0.f;
-        int ix, iy, iz;
-        float fx, fy, fz;
-        pm_cell(q.x, shift, wscale, ix, fx);
-        pm_cell(q.y, shift, wscale, iy, fy);
-        pm_cell(q.z, shift, wscale, iz, fz);
-        const int mask = ng - 1;
+    const int64_t wave = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) >> 6, nwaves = (gridDim.x * (int64_t)blockDim.x) >> 6;
+    for (int64_t base = wave * (64 * PM_RUN); base < n; base += nwaves * (64 * PM_RUN)) {
+        uint32_t ckey[8];  // the run carried over, per corner (uniform; ~0: none)
+        float cval[8];
 #pragma unroll
         for (int c = 0; c < 8; c++) {
-            const int dx = c >> 2, dy = (c >> 1) & 1, dz = c & 1;
-            float v = m * (dx ? fx : 1.f - fx) * (dy ? fy : 1.f - fy) * (dz ? fz : 1.f - fz);
-            const uint32_t key = act ? (uint32_t)((((ix + dx) & mask) * ng + ((iy + dy) & mask)) * ng + ((iz + dz) & mask))
-                                     : 0xffffffffu;
-#pragma unroll
-            for (int off = 1; off < 64; off <<= 1) {
-                const uint32_t ku = (uint32_t)__shfl_up((int)key, off);
-                const float vu = __shfl_up(v, off);
-                if (lane >= off && ku == key) v += vu;
-            }
-            const uint32_t kd = (uint32_t)__shfl_down((int)key, 1);
-            if (act && (lane == 63 || kd != key)) atomicAdd(&mesh[key], v);
+            ckey[c] = 0xffffffffu;
+            cval[c] = 0.f;
         }
+        for (int r = 0; r < PM_RUN; r++) {
+            const int64_t p = base + 64 * r + lane;
+            const bool act = p < n;
+            const uint4 q = act ? parts[p] : make_uint4(0u, 0u, 0u, 0u);
+            const float m = act ? __uint_as_float(q.w) : 0.f;
+            int ix, iy, iz;
+            float fx, fy, fz;
+            pm_cell(q.x, shift, wscale, ix, fx);
+            pm_cell(q.y, shift, wscale, iy, fy);
+            pm_cell(q.z, shift, wscale, iz, fz);
+            const int mask = ng - 1;
+#pragma unroll
+            for (int c = 0; c < 8; c++) {
+                const int dx = c >> 2, dy = (c >> 1) & 1, dz = c & 1;
+                float v = m * (dx ? fx : 1.f - fx) * (dy ? fy : 1.f - fy) * (dz ? fz : 1.f - fz);
+                const uint32_t key =
+                    act ? (uint32_t)((((ix + dx) & mask) * ng + ((iy + dy) & mask)) * ng + ((iz + dz) & mask)) : 0xffffffffu;
+                if (lane == 0 && ckey[c] != 0xffffffffu) {
+                    if (ckey[c] == key) v += cval[c];
+                    else atomicAdd(&mesh[ckey[c]], cval[c]);
+                }
+#pragma unroll
+                for (int off = 1; off < 64; off <<= 1) {
+                    const uint32_t ku = (uint32_t)__shfl_up((int)key, off);
+                    const float vu = __shfl_up(v, off);
+                    if (lane >= off && ku == key) v += vu;
+                }
+                const uint32_t kd = (uint32_t)__shfl_down((int)key, 1);
+                if (act && lane != 63 && kd != key) atomicAdd(&mesh[key], v);
+                ckey[c] = (uint32_t)__shfl((int)key, 63);
+                cval[c] = __shfl(v, 63);
+            }
+        }
+#pragma unroll
+        for (int c = 0; c < 8; c++)
+            if (lane == 0 && ckey[c] != 0xffffffffu) atomicAdd(&mesh[ckey[c]], cval[c]);
     }
 }
 
