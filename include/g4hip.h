@@ -85,9 +85,11 @@ typedef struct {
  *            node holds the target.  Nodes closer than h = 2.8 eps0 are
  *            always opened.  TreePM drops nodes whose nearest edge is farther
  *            than r_cut.  alpha_split = 1/(2 r_s).
- * group_size: most particles per 64-lane wavefront group (1..64; 0: 64).
- *            Small sets are walked in smaller groups (sqrt(n)/16, at least
- *            8) so that the chip is filled; results do not depend on it.
+ * group_size: particles per 64-lane wavefront group (1..64), or 0: chosen by
+ *            the number of particles (sqrt(n)/16, 8 to 64), so that a small
+ *            set fills the chip.  Opening decisions do not depend on it; the
+ *            order of each particle's FP64 sum does.  At one given size a
+ *            forest and the separate trees of its boxes agree bit for bit.
  * a_seed:    device, caller order, |a| per particle (nullable).
  * seed_from_tree: with a_seed NULL, 1 = use the |a| that the previous
  *            geometric (criterion 0) call left in this tree instead of

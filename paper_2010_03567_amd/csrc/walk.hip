@@ -958,27 +958,24 @@ __global__ void k_srtab(float4 *__restrict__ tab, int n)
                            (float)(2.0 * (f0 - f1) + d0 + d1));
 }
 
-// Targets per wavefront of n particles: the caller's group size (64 if it gives
-// none), but no more than sqrt(n)/16, at least 8.  A group is walked by one
-// wavefront from the root to the leaves, a serial chain of some hundred tree
-// entries, so with few particles groups of 64 leave most of the 1024 SIMDs without
-// work (8192 particles: 128 wavefronts), while with many particles small groups
-// repeat the traversal too often.  The best sizes found for n = 1500, 8192, 30 k,
-// 100 k, 300 k, 10^6, 2^21 are 2-4, 8, 8, 8-16, 24, 32-48, 64 (Newtonian and
-// TreePM; Ewald 5 k: 2, 110 k: 8-16), which grow like the square root.  Relative
-// walk at 64 and at the rule's size: 8192 Newtonian 0.64 and 0.27 ms, 50 k TreePM
+// Targets per wavefront of n particles where the caller leaves the choice to the library
+// (group_size 0): sqrt(n)/16, at least 8.  A group is walked by one wavefront from the root
+// to the leaves, a serial chain of some hundred tree entries, so with few particles groups
+// of 64 leave most of the 1024 SIMDs without work (8192 particles: 128 wavefronts), while
+// with many particles small groups repeat the traversal too often.  The best sizes found for
+// n = 1500, 8192, 30 k, 100 k, 300 k, 10^6, 2^21 are 2-4, 8, 8, 8-16, 24, 32-48, 64
+// (Newtonian and TreePM; Ewald 5 k: 2, 110 k: 8-16), which grow like the square root.
+// Relative walk at 64 and at the rule's size: 8192 Newtonian 0.64 and 0.27 ms, 50 k TreePM
 // 0.81 and 0.38, 110 k Ewald 5.3 and 3.3, 500 k TreePM 1.74 and 1.70.
-// Decisions are taken per target, so results do not depend on the size (the
-// FP64 sums only in their order).
-static int walk_group(int asked, int64_t n)
-{
-    return std::min(asked, (int)std::min(64.0, std::max(8.0, std::sqrt((double)n) / 16.0)));
-}
+// A size that the caller names is taken as it is: decisions are per target, but the order of
+// the FP64 sums follows the groups, and a forest and the separate trees of its boxes agree
+// bit for bit at one size only.
+static int walk_group(int64_t n) { return (int)std::min(64.0, std::max(8.0, std::sqrt((double)n) / 16.0)); }
 // A forest of this many particles fills the chip: its groups follow from all of
-// them.  In a smaller one each box is cut as its own tree would be (the same
-// forces bit for bit).  By box / by the total, ms per step: 24 boxes, 6.7e5
-// particles 4.08 / 3.73, 300 boxes, 6.3e5 7.0 / 2.2; by box / in groups of 64: 40
-// boxes, 2.0e5 2.1 / 2.2, 10 boxes, 8.5e4 1.3 / 2.0.
+// them.  In a smaller one each box is cut as its own tree would be.  By box / by
+// the total, ms per step: 24 boxes, 6.7e5 particles 4.08 / 3.73, 300 boxes, 6.3e5
+// 7.0 / 2.2; by box / in groups of 64: 40 boxes, 2.0e5 2.1 / 2.2, 10 boxes, 8.5e4
+// 1.3 / 2.0.
 #define WALK_FOREST_FULL (1 << 18)
 
 int g4_launch_walk(g4_ctx *ctx, g4_tree *t, const g4_walk_params *wp, int kernel, int criterion, double *ax,
@@ -992,8 +989,8 @@ int g4_launch_walk(g4_ctx *ctx, g4_tree *t, const g4_walk_params *wp, int kernel
     A.aseed = t->aseed;
     A.perm = t->perm1;
     A.n = t->n;
-    const int asked = wp->group_size > 0 && wp->group_size <= 64 ? wp->group_size : 64;
-    A.group = walk_group(asked, t->n);
+    const int asked = wp->group_size;  // 0 to 64
+    A.group = asked > 0 ? asked : walk_group(t->n);
     A.S = t->S;
     A.exclusion = wp->exclusion ? 1 : 0;
     A.order = wp->order;
@@ -1034,7 +1031,7 @@ int g4_launch_walk(g4_ctx *ctx, g4_tree *t, const g4_walk_params *wp, int kernel
     // interaction and pass counters only when the caller reads them: the kernel then skips
     // the per-lane counting as well
     A.stat = count ? t->ctr->stat + stat_slot : nullptr;
-    if (t->nbox > 1 && t->items_group != asked) {
+    if (t->nbox > 1 && (!t->nitems || t->items_group != asked)) {
         // work items of a forest: every box cut into groups; largest boxes first so the
         // persistent wavefronts finish together (longest-processing-time order)
         if (!t->items_host) {
@@ -1050,8 +1047,8 @@ int g4_launch_walk(g4_ctx *ctx, g4_tree *t, const g4_walk_params *wp, int kernel
         G4_HIP(ctx, hipStreamSynchronize(ctx->stream));
         int64_t k = 0;
         for (int b : order) {
-            const int group = t->n >= WALK_FOREST_FULL ? A.group
-                                                       : walk_group(asked, t->box_off[b + 1] - t->box_off[b]);
+            const int group = asked > 0 || t->n >= WALK_FOREST_FULL ? A.group
+                                                                     : walk_group(t->box_off[b + 1] - t->box_off[b]);
             for (int64_t f = t->box_off[b]; f < t->box_off[b + 1]; f += group) {
                 const int64_t c = std::min<int64_t>(group, t->box_off[b + 1] - f);
                 t->items_host[k++] = make_uint4((uint32_t)f, (uint32_t)c, (uint32_t)b, 0u);
