@@ -86,8 +86,8 @@ typedef struct {
  *            always opened.  TreePM drops nodes whose nearest edge is farther
  *            than r_cut.  alpha_split = 1/(2 r_s).
  * group_size: particles per 64-lane wavefront group (1..64), or 0: chosen by
- *            the number of particles (sqrt(n)/16, 8 to 64), so that a small
- *            set fills the chip.  Opening decisions do not depend on it; the
+ *            the number of particles (sqrt(n)/16, 8 to 64; 64 for forests of
+ *            many short boxes), so that a small set fills the chip.  Opening decisions do not depend on it; the
  *            order of each particle's FP64 sum does.  At one given size a
  *            forest and the separate trees of its boxes agree bit for bit.
  * a_seed:    device, caller order, |a| per particle (nullable).

@@ -970,13 +970,19 @@ __global__ void k_srtab(float4 *__restrict__ tab, int n)
 // A size that the caller names is taken as it is: decisions are per target, but the order of
 // the FP64 sums follows the groups, and a forest and the separate trees of its boxes agree
 // bit for bit at one size only.
-static int walk_group(int64_t n) { return (int)std::min(64.0, std::max(8.0, std::sqrt((double)n) / 16.0)); }
-// A forest of this many particles fills the chip: its groups follow from all of
-// them.  In a smaller one each box is cut as its own tree would be.  By box / by
-// the total, ms per step: 24 boxes, 6.7e5 particles 4.08 / 3.73, 300 boxes, 6.3e5
-// 7.0 / 2.2; by box / in groups of 64: 40 boxes, 2.0e5 2.1 / 2.2, 10 boxes, 8.5e4
-// 1.3 / 2.0.
-#define WALK_FOREST_FULL (1 << 18)
+//
+// A forest is cut by its total, which says how many wavefronts it gives.  Where its
+// boxes are short (fewer than 512 particles on average) and groups of 64 give every
+// SIMD a wavefront already, smaller ones only repeat the few entries of a short walk.
+// Relative walk, ms, in groups of 8 / of the total's size / of 64: 320 boxes of 800
+// 1.06 / 0.73 / 0.74, 100 of 2300 1.09 / 0.91 / 1.12, 40 of 6000 1.43 / 1.21 / 1.55, 10 of
+// 8500 0.87 / 0.92 / 1.64, 300 of 2100 2.38 / 1.66 / 1.72, 24 of 28 k 4.10 / 3.15 / 3.24;
+// 1000 boxes of 250 0.97 / 0.52 / 0.41, 2000 of 30 0.40 / 0.25 / 0.14.
+static int walk_group(int64_t n, int64_t nbox)
+{
+    if (nbox > 1 && n < 512 * nbox && std::max(nbox, n / 64) >= 1024) return 64;
+    return (int)std::min(64.0, std::max(8.0, std::sqrt((double)n) / 16.0));
+}
 
 int g4_launch_walk(g4_ctx *ctx, g4_tree *t, const g4_walk_params *wp, int kernel, int criterion, double *ax,
                    double *ay, double *az, double *pot, uint32_t *counts, float *aout_caller, float *aout_sorted,
@@ -989,8 +995,7 @@ int g4_launch_walk(g4_ctx *ctx, g4_tree *t, const g4_walk_params *wp, int kernel
     A.aseed = t->aseed;
     A.perm = t->perm1;
     A.n = t->n;
-    const int asked = wp->group_size;  // 0 to 64
-    A.group = asked > 0 ? asked : walk_group(t->n);
+    A.group = wp->group_size > 0 ? wp->group_size : walk_group(t->n, t->nbox);
     A.S = t->S;
     A.exclusion = wp->exclusion ? 1 : 0;
     A.order = wp->order;
@@ -1031,7 +1036,7 @@ int g4_launch_walk(g4_ctx *ctx, g4_tree *t, const g4_walk_params *wp, int kernel
     // interaction and pass counters only when the caller reads them: the kernel then skips
     // the per-lane counting as well
     A.stat = count ? t->ctr->stat + stat_slot : nullptr;
-    if (t->nbox > 1 && (!t->nitems || t->items_group != asked)) {
+    if (t->nbox > 1 && t->items_group != A.group) {
         // work items of a forest: every box cut into groups; largest boxes first so the
         // persistent wavefronts finish together (longest-processing-time order)
         if (!t->items_host) {
@@ -1046,16 +1051,13 @@ int g4_launch_walk(g4_ctx *ctx, g4_tree *t, const g4_walk_params *wp, int kernel
         // wait for earlier work that may still read the previous items
         G4_HIP(ctx, hipStreamSynchronize(ctx->stream));
         int64_t k = 0;
-        for (int b : order) {
-            const int group = asked > 0 || t->n >= WALK_FOREST_FULL ? A.group
-                                                                     : walk_group(t->box_off[b + 1] - t->box_off[b]);
-            for (int64_t f = t->box_off[b]; f < t->box_off[b + 1]; f += group) {
-                const int64_t c = std::min<int64_t>(group, t->box_off[b + 1] - f);
+        for (int b : order)
+            for (int64_t f = t->box_off[b]; f < t->box_off[b + 1]; f += A.group) {
+                const int64_t c = std::min<int64_t>(A.group, t->box_off[b + 1] - f);
                 t->items_host[k++] = make_uint4((uint32_t)f, (uint32_t)c, (uint32_t)b, 0u);
             }
-        }
         t->nitems = (uint32_t)k;
-        t->items_group = asked;
+        t->items_group = A.group;
         G4_HIP(ctx, hipMemcpyAsync(t->items, t->items_host, (size_t)k * sizeof(uint4), hipMemcpyHostToDevice,
                                    ctx->stream));
     }

@@ -63,3 +63,15 @@ def test_named_group_size_is_used(g):
     e = {s: g.g4_treepm_shortrange(ctx, t, g.walk_params(group_size=s, **kw), want_stats=True)["stats"]["w_entry"]
          for s in (64, 32, 8)}
     assert e[8] > e[32] > e[64] and e[8] >= 2 * e[64], e
+
+
+# boxes, particles of each, and the group that the rule gives
+@pytest.mark.parametrize("nbox,size,group", [(320, 800, 31), (1000, 250, 64), (1100, 30, 64), (12, 2000, 9)])
+def test_unset_group_of_a_forest_follows_its_total(g, nbox, size, group):
+    """With the size left open a forest is cut by its total (31 a group for 2.56e5 particles)
+    or, with many short boxes, into groups of 64; never box by box into groups of 8."""
+    ctx = g.Context()
+    off, f, xyz, mass, tp = make_forest(g, ctx, [size] * nbox)
+    e = {s: g.g4_treepm_shortrange(ctx, f, g.walk_params(group_size=s, **{**KW, "criterion": 0}),
+                                   want_stats=True)["stats"]["w_entry"] for s in (0, group)}
+    assert e[0] == e[group], e
