@@ -256,13 +256,10 @@ __device__ __forceinline__ void eval_high(const float *o, const double *u4, floa
 
 #define NUM_LEAF (1u << 31)  // leaf bit of VisitRec::numleaf
 // Entries with fewer (child, target) slots than this skip the decisions for the
-// whole group (their cost per entry outweighs the visit passes they save), except
-// full ones of the first levels, where a group of any size can use or drop whole
-// octants of the box.  Groups of 8 to 15 targets reach 128 slots nowhere; taking the
-// decisions in all their full entries made 8192 particles 7 % and 50 k 6 % slower, down
-// to level 5 2.6 and 2.4 %, to level 3 less than 1 %.
+// whole group (their cost per entry outweighs the visit passes they save); groups of
+// fewer than 16 targets never reach it (with decisions in all their full entries 8192
+// particles in groups of 8 were 7 % and 50 k 6 % slower).
 #define WK_GROUP_MIN_SLOTS 128
-#define WK_GROUP_TOP 3
 
 // Per-child visit record, staged in LDS for the passes over one entry.
 struct __attribute__((aligned(16))) VisitRec {
@@ -688,9 +685,7 @@ __global__ __launch_bounds__(256, WALK_MIN_WAVES(KER, POT, HI)) void k_walk(cons
             v_numleaf = r.numleaf;
             W.rec[lane] = r;
             const float gamin = W.gamin;
-            const uint32_t enough = level <= WK_GROUP_TOP ? min((uint32_t)WK_GROUP_MIN_SLOTS, 8 * gcount)
-                                                          : (uint32_t)WK_GROUP_MIN_SLOTS;
-            if (c * k >= enough && !(A.exclusion & 2) && level > 0 && gamin >= 0.f) {
+            if (c * k >= WK_GROUP_MIN_SLOTS && !(A.exclusion & 2) && level > 0 && gamin >= 0.f) {
                 v_dec = group_decision<KER, CRIT, ORD3, HI>(A, nd, r.crit, r.hl, r.lm1, W.tgt[0], W.gbox, gamin);
                 if (v_dec == 4u) {
                     // left to the targets, none of which can see the cube beyond r_cut

@@ -75,3 +75,37 @@ def test_unset_group_of_a_forest_follows_its_total(g, nbox, size, group):
     e = {s: g.g4_treepm_shortrange(ctx, f, g.walk_params(group_size=s, **{**KW, "criterion": 0}),
                                    want_stats=True)["stats"]["w_entry"] for s in (0, group)}
     assert e[0] == e[group], e
+
+
+# 16 targets and eight siblings are the fewest that make 128 slots
+@pytest.mark.parametrize("kind", ["box", "plummer"])
+@pytest.mark.parametrize("criterion", [0, 1])
+def test_group_decisions_by_group_size(g, kind, criterion, monkeypatch):
+    """Decisions for whole groups start at 128 (node, target) slots: groups of 15 take none, groups of
+    16 to 64 take some, and counts and forces equal those of a walk without any."""
+    ctx = g.Context()
+    n = 20011
+    if kind == "box":
+        pos, tp = workloads.clustered_box(n, seed=6, nhalo=40).pos, g.tree_params(True, 1.0, leaf_max=8)
+        kw = dict(kernel=1, r_s=0.02, r_cut=0.14, eps0=0.002)
+    else:
+        pos, tp = workloads.plummer(n, seed=6).pos, g.tree_params(False, 44.0, origin=(-22.0,) * 3, leaf_max=8)
+        kw = dict(kernel=0, eps0=0.01)
+    xyz = g.g4_quantize(ctx, torch.from_numpy(np.ascontiguousarray(pos)).cuda(), tp)
+    t = g.g4_build_tree(ctx, g.particles(*xyz, torch.full((n,), 1.0 / n, device="cuda")), tp)
+    g.g4_compute_multipoles(ctx, t, 3)
+    geo = g.g4_tree_force(ctx, t, g.walk_params(criterion=0, theta=0.7, **kw))
+    seed = torch.sqrt(geo["ax"] ** 2 + geo["ay"] ** 2 + geo["az"] ** 2).float()
+    crit = dict(criterion=1, alpha=0.002, a_seed=seed) if criterion else dict(criterion=0, theta=0.6)
+    for group in (15, 16, 33, 63, 64):
+        out = []
+        for per_target in ("0", "1"):
+            monkeypatch.setenv("G4_WALK_PER_TARGET", per_target)
+            out.append(g.g4_tree_force(ctx, t, g.walk_params(group_size=group, **crit, **kw), want_counts=True,
+                                       want_stats=True))
+        a, b = out
+        assert (a["stats"]["n_group_use"] > 0) == (group >= 16) and b["stats"]["n_group_use"] == 0, group
+        assert torch.equal(a["counts"], b["counts"])
+        for k in ("ax", "ay", "az"):
+            # the same FP32 terms in FP64 sums of another order, some 10^3 of them
+            assert (a[k] - b[k]).abs().max().item() <= 1e-12 * b[k].abs().max().item(), (group, k)
