@@ -20,6 +20,7 @@ struct DirectArgs {
     int64_t n;
     const int64_t *targets;
     int64_t nt;
+    int64_t t0;  // first target of this launch
     double unit, h, hinv, asplit, rskip2, rcut2, G, L;
     float near2;  // squared reach of a pair in grid steps, rounded up (kernel 1, or truncated sums)
     uint32_t reach16;  // the reach in steps of 2^16 grid units, rounded up, plus one for the dropped bits (FAR)
@@ -168,7 +169,7 @@ __global__ __launch_bounds__(64 * NW, FAR ? 4 : 1) void k_direct(const DirectArg
     __shared__ uint32_t seen[FAR ? NW : 1][FAR ? 64 + 64 * DIRECT_STEP : 1];  // pending sources
     __shared__ uint32_t tx[TB], ty[TB], tz[TB];
     __shared__ int64_t ti[TB];
-    const int64_t q0 = blockIdx.x * (int64_t)TB;
+    const int64_t q0 = A.t0 + blockIdx.x * (int64_t)TB;
     const int nt = (int)min((int64_t)TB, A.nt - q0);
     const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     if (threadIdx.x < TB) {
@@ -379,15 +380,25 @@ __global__ __launch_bounds__(DT) void k_direct_ewald(const DirectArgs A)
     }
 }
 
+// Blocks of one launch: a grid holds fewer than 2^32 threads, which 2^26 targets reach
+// at 8 targets to a block of 512.  More targets take more launches, one after the other.
+#define DIRECT_BLOCKS ((int64_t)1 << 22)
+
 template <int KER, int TB, bool FAR>
-static void launch_direct_tb(const DirectArgs &A, hipStream_t s)
+static void launch_direct_tb(DirectArgs A, hipStream_t s)
 {
     // few targets: larger blocks, so that a block's lanes are more of the chip and its near
     // pairs, which differ much from block to block, more evenly spread (reach 0.075: 300
     // targets of 10^6 0.66 ms at 16 wavefronts, 0.68 at 8, 0.97 at 4; 10^4 targets 4.92, 4.28, 4.91)
     const int64_t blocks = (A.nt + TB - 1) / TB;
-    if (blocks < 1024) k_direct<KER, TB, 16, FAR><<<(unsigned)blocks, 1024, 0, s>>>(A);
-    else k_direct<KER, TB, FAR ? 8 : 4, FAR><<<(unsigned)blocks, FAR ? 512 : 256, 0, s>>>(A);
+    if (blocks < 1024) {
+        k_direct<KER, TB, 16, FAR><<<(unsigned)blocks, 1024, 0, s>>>(A);
+        return;
+    }
+    for (int64_t b = 0; b < blocks; b += DIRECT_BLOCKS) {
+        A.t0 = b * TB;
+        k_direct<KER, TB, FAR ? 8 : 4, FAR><<<(unsigned)std::min(DIRECT_BLOCKS, blocks - b), FAR ? 512 : 256, 0, s>>>(A);
+    }
 }
 
 // Targets per block: 8 (4 without lists, where the sums stay in registers)
@@ -420,6 +431,7 @@ int g4_launch_direct(g4_ctx *ctx, const g4_particles *p, const g4_tree_params *t
     A.x = p->x; A.y = p->y; A.z = p->z; A.m = p->mass; A.n = p->n;
     A.targets = targets;
     A.nt = targets ? ntargets : p->n;
+    A.t0 = 0;
     A.unit = tp->box / (tp->periodic ? 4294967296.0 : 2147483648.0);
     A.L = tp->box;
     A.h = 2.8 * wp->eps0;
