@@ -630,15 +630,16 @@ __device__ __forceinline__ void psi_mirror(float D[20])
 // sources, the top ones many more, which one thread per node took one by one:
 // 30 k particles 2.38 -> 0.10 ms.
 #define M2L_ROW 21  // 20 terms and the mass
+#define FMM_M2L_NODES ((int64_t)1 << 24)  // nodes of one launch: a grid holds fewer than 2^32 threads
 
 template <bool EW>
-__global__ __launch_bounds__(256) void k_fmm_m2l(FmmArgs A, const uint32_t *__restrict__ start,
+__global__ __launch_bounds__(256) void k_fmm_m2l(FmmArgs A, uint32_t q0, const uint32_t *__restrict__ start,
                                                  const uint32_t *__restrict__ end, float *__restrict__ F)
 {
     __shared__ float terms[4][64 * M2L_ROW], psi[EW ? 4 : 1][EW ? 64 * M2L_ROW : 1];
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     const uint32_t nn = A.ctr->node_count;
-    const uint32_t q = blockIdx.x * 4 + wv;
+    const uint32_t q = q0 + blockIdx.x * 4 + wv;
     if (q >= nn) return;
     float *T = terms[wv], *P = psi[EW ? wv : 0];
     const WNode w = A.wn[q];
@@ -2291,8 +2292,11 @@ int g4_launch_fmm(g4_ctx *ctx, g4_tree *t, const g4_fmm_params *fp, double facto
     A.nval = nv2;
     A.pval = pv2;
     float *F = (float *)(b + L.F);
-    if (fp->kernel == 2) k_fmm_m2l<true><<<(unsigned)((nn_host + 3) / 4), 256, 0, s>>>(A, nstart, nend, F);
-    else k_fmm_m2l<false><<<(unsigned)((nn_host + 3) / 4), 256, 0, s>>>(A, nstart, nend, F);
+    for (int64_t q0 = 0; q0 < nn_host; q0 += FMM_M2L_NODES) {
+        const unsigned mb = (unsigned)((std::min(FMM_M2L_NODES, nn_host - q0) + 3) / 4);
+        if (fp->kernel == 2) k_fmm_m2l<true><<<mb, 256, 0, s>>>(A, (uint32_t)q0, nstart, nend, F);
+        else k_fmm_m2l<false><<<mb, 256, 0, s>>>(A, (uint32_t)q0, nstart, nend, F);
+    }
     const int maxd = t->tp.max_depth;
     for (int l = 1; l <= maxd && levels[l]; l++) k_fmm_l2l<<<l2l_grid(levels[l]), 256, 0, s>>>(A, l, F);
     uint32_t *leafid = (uint32_t *)(b + L.leafid);
