@@ -11,8 +11,9 @@
 // Static device scratch of the FMM entry point that allocates nothing
 // (g4_fmm_force_noalloc).  Every device the library runs on holds one copy
 // until the process ends.  In host code `scratch` is only a stand-in symbol:
-// its device address comes from hipGetSymbolAddress, once per device.
-#define G4_NOALLOC_SCRATCH_BYTES ((size_t)64 << 20)
+// its device address comes from hipGetSymbolAddress, once per device.  64 MiB are
+// for the lists, fields and accumulators, whatever the counters in front of them take.
+#define G4_NOALLOC_SCRATCH_BYTES (((size_t)64 << 20) + G4_FMM_COUNTER_BYTES)
 #define G4_MAX_DEVICES 64
 static __device__ __align__(256) unsigned char scratch[G4_NOALLOC_SCRATCH_BYTES];
 static void *g_scratch_ptr[G4_MAX_DEVICES];

@@ -52,7 +52,8 @@
 #define FMM_WORDS (FMM_FRONT + 65)
 #define FMM_STATS 256   // first word of the interaction counts
 #define FMM_STAT_SLOTS 32      // copies of them, each in a cache line of its own
-#define FMM_CNT_BYTES (4 * FMM_STATS + 128 * FMM_STAT_SLOTS)
+#define FMM_CNT_BYTES G4_FMM_COUNTER_BYTES
+static_assert(FMM_CNT_BYTES == 4 * FMM_STATS + 128 * FMM_STAT_SLOTS, "counter block");
 
 struct FmmArgs {
     const WNode *wn;

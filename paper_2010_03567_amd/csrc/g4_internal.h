@@ -112,6 +112,9 @@ struct g4_tree {
 #define G4_FLAG_FMM_STACK 8u
 #define G4_FLAG_FATAL (2u | G4_FLAG_WALK_STACK | G4_FLAG_FMM_STACK)
 
+// Counters of an FMM call (list lengths, tree sizes, interaction counts), the first part of its workspace.
+#define G4_FMM_COUNTER_BYTES 5120
+
 // Layout of a tree workspace (byte offsets).
 struct WsLayout {
     size_t ctr, keys0, keys1, perm0, perm1, parts, bfirst, bcount, parent, wn, q3, mom, aseed, leafof, spill,

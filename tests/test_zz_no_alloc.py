@@ -67,3 +67,43 @@ def test_noalloc_fmm_rejects_tree_beyond_scratch(g, ctx):
     with pytest.raises(g.G4Error) as e:
         g.g4_fmm_force_noalloc(ctx, tree, fp)
     assert e.value.code == g.G4_EINVAL and "static FMM scratch" in str(e.value)
+
+
+# sorted-list mode: about 7 kB a particle, so the leaf size picks a tree that ends within the last few
+# kB; large leaves keep its lists within list factor 1
+@pytest.mark.parametrize("det", [0, 1])
+def test_noalloc_fmm_has_64_mib_behind_its_counters(g, ctx, det):
+    """The scratch holds 64 MiB beside the call's counters (5 KiB): a tree whose lists, fields and
+    accumulators end within the last 2 KiB of those 64 MiB is accepted, and gives the forces of the
+    call with a workspace."""
+    limit, counters = 64 << 20, 5120
+    kw = dict(kernel=1, theta=0.5, r_s=0.004, r_cut=0.018, eps0=1e-4, deterministic=det)
+
+    def build(n, leaf):
+        rng = np.random.default_rng(5)
+        tp = g.tree_params(True, 1.0, leaf_max=leaf)
+        x, y, z = g.g4_quantize(ctx, torch.from_numpy(rng.random((n, 3))).cuda(), tp)
+        return g.g4_build_tree(ctx, g.particles(x, y, z, torch.full((n,), 1.0 / n, device="cuda")), tp)
+
+    found = None
+    for leaf in range(200, 400) if det else range(16, 40):
+        lo, hi = 1000, 400000  # the most particles that fit
+        while hi - lo > 1:
+            mid = (lo + hi) // 2
+            if g.g4_fmm_workspace_bytes(build(mid, leaf), g.fmm_params(**kw)) - counters <= limit:
+                lo = mid
+            else:
+                hi = mid
+        if g.g4_fmm_workspace_bytes(build(lo, leaf), g.fmm_params(**kw)) - counters > limit - 2048:
+            found = (lo, leaf)
+            break
+    assert found, "no tree ends there"
+    tree = build(*found)
+    g.g4_compute_multipoles(ctx, tree, 3)
+    fp = g.fmm_params(**kw)
+    got, ref = g.g4_fmm_force_noalloc(ctx, tree, fp), g.g4_fmm_force(ctx, tree, fp)
+    if det:
+        assert np.array_equal(_a(got), _a(ref))
+    else:
+        e = workloads.relative_errors(_a(got), _a(ref))
+        assert np.median(e) <= 1e-6 and np.percentile(e, 99.9) <= 1e-3, (np.median(e), e.max())
