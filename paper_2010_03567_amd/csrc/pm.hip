@@ -46,7 +46,8 @@ __global__ void k_pm_tables(float2 *__restrict__ tw, float *__restrict__ gt, int
     tw[i] = make_float2((float)c, (float)s);
     const int n = i < ng / 2 ? i : i - ng;
     const double k = 2.0 * M_PI * n / box, u = M_PI * n / ng, w = n ? sin(u) / u : 1.0;
-    gt[i] = (float)(exp(-k * k * r_s * r_s) / (w * w * w * w));
+    // an infinite split scale leaves the mean alone, which the force drops: zero, not NaN
+    gt[i] = n ? (float)(exp(-k * k * r_s * r_s) / (w * w * w * w)) : 1.f;
 }
 
 __global__ void k_pm_clear(float4 *__restrict__ m, size_t nvec)

@@ -91,3 +91,40 @@ def test_pm_sizes(g, ng, n, keys):
                              out=tuple(torch.ones_like(out["ax"]) for _ in range(4)))
     for c in ("ax", "ay", "az", "pot"):
         assert (more[c] - 1 - out[c]).abs().max().item() <= 1e-4 * max(rms.item(), out[c].abs().max().item())
+
+
+@pytest.mark.parametrize("ng", [16, 64])
+def test_pm_of_one_particle(g, ng):
+    """A single particle feels no force but its own mesh force, which vanishes up to rounding; its
+    potential is that of the 64-bit reference; accumulating adds the same."""
+    ctx = g.Context()
+    box, G = 2.5, 0.7
+    tp = g.tree_params(True, box, leaf_max=16)
+    pos = torch.tensor([[0.3, 1.9, 2.4]], dtype=torch.float64, device="cuda")
+    m = torch.tensor([1.5], device="cuda")
+    x, y, z = g.g4_quantize(ctx, pos, tp)
+    tree = g.g4_build_tree(ctx, g.particles(x, y, z, m), tp)
+    r_s = 1.25 * box / ng
+    out = g.g4_pm_longrange(ctx, tree, g.pm_params(ng, r_s, G), want_pot=True)
+    X = torch.stack([v.long() & 0xffffffff for v in (x, y, z)], 1)
+    acc, pot = reference(X, m.double(), ng, box, r_s, G)
+    assert (out["pot"] - pot).abs().item() <= 3e-6 * pot.abs().item()
+    # the antisymmetric differences cancel to the rounding of the potential over a cell
+    for k, c in enumerate(("ax", "ay", "az")):
+        assert (out[c] - acc[k]).abs().item() <= 1e-5 * pot.abs().item() * ng / box, c
+    more = g.g4_pm_longrange(ctx, tree, g.pm_params(ng, r_s, G), accumulate=True,
+                             out=tuple(torch.ones_like(out["ax"]) for _ in range(4)))
+    for c in ("ax", "ay", "az", "pot"):
+        assert (more[c] - 1 - out[c]).abs().item() <= 1e-5 * pot.abs().item() * ng / box, c
+
+
+def test_pm_of_an_infinite_split_scale(g):
+    """exp(-k^2 r_s^2) is zero for every wave but k = 0, which the force drops: all zero."""
+    ctx = g.Context()
+    tp = g.tree_params(True, 1.0, leaf_max=16)
+    ps = workloads.clustered_box(1000, seed=3, nhalo=4)
+    x, y, z = g.g4_quantize(ctx, torch.from_numpy(ps.pos).cuda(), tp)
+    tree = g.g4_build_tree(ctx, g.particles(x, y, z, torch.ones(1000, device="cuda")), tp)
+    out = g.g4_pm_longrange(ctx, tree, g.pm_params(32, math.inf), want_pot=True)
+    for c in ("ax", "ay", "az", "pot"):
+        assert torch.all(out[c] == 0), c
