@@ -68,15 +68,25 @@ __device__ __forceinline__ void pm_cell(uint32_t X, int shift, float wscale, int
 // corner is the same shift of it).  Every corner's contributions are summed
 // over such runs by a segmented scan across the wavefront and the last lane
 // of a run issues the one atomic: in haloes most atomics disappear.  A wavefront
-// takes PM_RUN times 64 consecutive particles and carries the run at the end of each 64
-// over to the next, which also leaves fewer sums to the order of the atomics.
+// takes RUN times 64 consecutive particles and carries the run at the end of each 64
+// over to the next.
+//
+// The atomics come in any order.  Where the mesh is small they add in FP64, rounded
+// once after (k_pm_round): two calls then differ in no bit but for a rare flip of that
+// rounding.  With FP32 sums the particle that differs most between two calls of
+// 30000 particles at 32^3 was off by 6e-5 of its force in the median, and by
+// more than 1e-4 in 16 of 100 pairs of calls.  On larger meshes the wider sums would
+// cost memory traffic (8 bytes more cleared and read a point), so there the longer runs
+// leave fewer sums to the order instead.
+#define PM_WIDE 64  // largest mesh side with FP64 sums
 #define PM_RUN 4
+template <typename T, int RUN>
 __global__ void k_pm_deposit(const uint4 *__restrict__ parts, int64_t n, int ng, int shift, float wscale,
-                             float *__restrict__ mesh)
+                             T *__restrict__ mesh)
 {
     const int lane = threadIdx.x & 63;
     const int64_t wave = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) >> 6, nwaves = (gridDim.x * (int64_t)blockDim.x) >> 6;
-    for (int64_t base = wave * (64 * PM_RUN); base < n; base += nwaves * (64 * PM_RUN)) {
+    for (int64_t base = wave * (64 * RUN); base < n; base += nwaves * (64 * RUN)) {
         uint32_t ckey[8];  // the run carried over, per corner (uniform; ~0: none)
         float cval[8];
 #pragma unroll
@@ -84,7 +94,7 @@ __global__ void k_pm_deposit(const uint4 *__restrict__ parts, int64_t n, int ng,
             ckey[c] = 0xffffffffu;
             cval[c] = 0.f;
         }
-        for (int r = 0; r < PM_RUN; r++) {
+        for (int r = 0; r < RUN; r++) {
             const int64_t p = base + 64 * r + lane;
             const bool act = p < n;
             const uint4 q = act ? parts[p] : make_uint4(0u, 0u, 0u, 0u);
@@ -103,7 +113,7 @@ __global__ void k_pm_deposit(const uint4 *__restrict__ parts, int64_t n, int ng,
                     act ? (uint32_t)((((ix + dx) & mask) * ng + ((iy + dy) & mask)) * ng + ((iz + dz) & mask)) : 0xffffffffu;
                 if (lane == 0 && ckey[c] != 0xffffffffu) {
                     if (ckey[c] == key) v += cval[c];
-                    else atomicAdd(&mesh[ckey[c]], cval[c]);
+                    else atomicAdd(&mesh[ckey[c]], (T)cval[c]);
                 }
 #pragma unroll
                 for (int off = 1; off < 64; off <<= 1) {
@@ -112,14 +122,22 @@ __global__ void k_pm_deposit(const uint4 *__restrict__ parts, int64_t n, int ng,
                     if (lane >= off && ku == key) v += vu;
                 }
                 const uint32_t kd = (uint32_t)__shfl_down((int)key, 1);
-                if (act && lane != 63 && kd != key) atomicAdd(&mesh[key], v);
+                if (act && lane != 63 && kd != key) atomicAdd(&mesh[key], (T)v);
                 ckey[c] = (uint32_t)__shfl((int)key, 63);
                 cval[c] = __shfl(v, 63);
             }
         }
 #pragma unroll
         for (int c = 0; c < 8; c++)
-            if (lane == 0 && ckey[c] != 0xffffffffu) atomicAdd(&mesh[ckey[c]], cval[c]);
+            if (lane == 0 && ckey[c] != 0xffffffffu) atomicAdd(&mesh[ckey[c]], (T)cval[c]);
+    }
+}
+
+__global__ void k_pm_round(const double2 *__restrict__ wide, size_t npair, float2 *__restrict__ mesh)
+{
+    for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < npair; i += (size_t)gridDim.x * blockDim.x) {
+        const double2 v = wide[i];
+        mesh[i] = make_float2((float)v.x, (float)v.y);
     }
 }
 
@@ -643,8 +661,9 @@ int g4_launch_pm(g4_ctx *ctx, const g4_tree *t, const g4_pm_params *pp, void *ws
     hipStream_t s = ctx->stream;
     const int shift = 32 - lg;
     const float wscale = ldexpf(1.f, -shift);
-    k_pm_tables<<<(ng + 255) / 256, 256, 0, s>>>(tw, gt, ng, t->tp.box, pp->r_s);
-    k_pm_clear<<<(unsigned)std::min<size_t>(4096, (ncell / 4 + 255) / 256), 256, 0, s>>>((float4 *)phi, ncell / 4);
+    auto clear = [&](void *p, size_t bytes) {
+        k_pm_clear<<<(unsigned)std::min<size_t>(4096, (bytes / 16 + 255) / 256), 256, 0, s>>>((float4 *)p, bytes / 16);
+    };
     const int64_t n = t->n;
     const unsigned pblocks = (unsigned)std::min<int64_t>(8192, (n + 255) / 256);
     // work items of the tiles, if the particles are dense enough for them and the lists fit
@@ -654,15 +673,26 @@ int g4_launch_pm(g4_ctx *ctx, const g4_tree *t, const g4_pm_params *pp, void *ws
     uint4 *items = (uint4 *)(b + L.spare + 256 + ((size_t)ncube + 1 + 63) / 64 * 256);
     const bool tiles = ncube && n >= (int64_t)PM_TILE_MIN * ncube && n >= (ng >= 128 ? PM_TILE_N / 3 : PM_TILE_N) &&
                        (char *)(items + max_items) <= b + L.total;
+    // the FP64 mesh lies behind the real one, where the spectrum and the tables come later
+    const bool wide = !tiles && ng <= PM_WIDE && L.half + ncell * sizeof(double) <= L.total;
     if (tiles) {
+        clear(phi, ncell * 4);
         k_pm_starts<<<(unsigned)((n + 1 + 255) / 256), 256, 0, s>>>(t->keys1, n, 3 * (G4_MAXLEV - lg + PM_CUBE_BITS), ncube,
                                                                   start, nitems);
         k_pm_items<<<(ncube + 255) / 256, 256, 0, s>>>(start, ncube, items, nitems);
         k_pm_deposit_tile<<<(unsigned)max_items, PM_DEP_THREADS, 0, s>>>(t->parts, items, nitems, ng, lg, shift, wscale,
                                                                          phi);
+    } else if (wide) {
+        double *mesh = (double *)(b + L.half);
+        clear(mesh, ncell * 8);
+        k_pm_deposit<double, 1><<<pblocks, 256, 0, s>>>(t->parts, n, ng, shift, wscale, mesh);
+        k_pm_round<<<(unsigned)std::min<size_t>(1024, (ncell / 2 + 255) / 256), 256, 0, s>>>((const double2 *)mesh, ncell / 2,
+                                                                                          (float2 *)phi);
     } else {
-        k_pm_deposit<<<pblocks, 256, 0, s>>>(t->parts, n, ng, shift, wscale, phi);
+        clear(phi, ncell * 4);
+        k_pm_deposit<float, PM_RUN><<<pblocks, 256, 0, s>>>(t->parts, n, ng, shift, wscale, phi);
     }
+    k_pm_tables<<<(ng + 255) / 256, 256, 0, s>>>(tw, gt, ng, t->tp.box, pp->r_s);
     // -G 4 pi / V / (2 pi / L)^2: the sum over wave numbers in units of 2 pi / L
     const float pref = (float)(-pp->G / (M_PI * t->tp.box));
     switch (lg) {
