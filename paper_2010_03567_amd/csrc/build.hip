@@ -699,14 +699,16 @@ __global__ __launch_bounds__(512) void k_moments_block(const DevCounters *__rest
     }
 }
 
-// Levels 0 to MOM_TOP hold at most 73 nodes (per box) and the levels from
-// MOM_DEEP on of a small set few or none, also where the set is the dense core of a
-// larger one: one block takes each of these ranges, a launch instead of one per level.
-// 8192 Plummer particles, leaf 16, 90 us (83 with the block from level 13 on); the same
-// in a fiftieth of the space, 10 k of them 108 us and 30 k 118 (180 and 404 from level 13 on).
+// Levels 0 to MOM_TOP hold at most 73 nodes (per box): one block takes them, a launch
+// instead of one per level.  So do the levels from MOM_DEEP on of a set of at most
+// MOM_DEEP_N particles.  A larger set may have thousands of nodes that deep, where it is
+// the dense core of a larger one, and 64 groups of lanes are too few for them: 16384
+// particles in 10^-4 of the box side, leaf 4, 155 us with a launch per level and 707 with
+// the block (leaf 16: 144, 353); 1024 in 10^-4, leaf 1, 181, 200; 500 184, 168; ordinary
+// sets of 1000 87, 78, of 8192 (leaf 16) 97, 91.
 #define MOM_TOP 2
 #define MOM_DEEP 17
-#define MOM_DEEP_N 16384  // a denser set may have many nodes that deep
+#define MOM_DEEP_N 512
 
 int g4_launch_moments(g4_ctx *ctx, g4_tree *t)
 {
