@@ -259,17 +259,19 @@ __global__ __launch_bounds__(THREADS) void k_rs_scatter(const K *__restrict__ ki
     const uint32_t valid_n = (uint32_t)std::min<int64_t>(TILE, n - b0);
     for (uint32_t j0 = 0; j0 < valid_n; j0 += THREADS) {
         const uint32_t j = j0 + threadIdx.x;
-        uint32_t slot = 0xffffffffu;  // of the next digit's table
+        K k = 0;
+        uint32_t o = 0;
         if (j < valid_n) {
-            const K k = skey[j];
+            k = skey[j];
             const uint32_t d = rs_digit(k, shift);
-            const uint32_t o = gpos[d] + (j - bpre[d]);
+            o = gpos[d] + (j - bpre[d]);
             kout[o] = k;
             vout[o] = sval[j];
-            slot = o / TILE * RS_BINS + rs_digit(k, shift + RS_BITS);
         }
         if constexpr (SMALL)
             if (next) {
+                // slot of the next digit's table; there is one, so shift + RS_BITS is below the key's width
+                const uint32_t slot = j < valid_n ? o / TILE * RS_BINS + rs_digit(k, shift + RS_BITS) : 0xffffffffu;
                 // one addition per run of equal slots in the wavefront: keys that share a digit
                 // would otherwise queue on one address
                 const uint32_t up = (uint32_t)__shfl_up((int)slot, 1);
