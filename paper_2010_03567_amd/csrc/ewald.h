@@ -108,7 +108,7 @@ typedef float ew_f4 __attribute__((ext_vector_type(4)));
 // 74 % of the time, VALU 35 %): tree and walks of 48^3 particles 4.72 -> 4.08 ms, of 20 k
 // 1.40 -> 1.15.  Where nine vectors of a row are enough (particle pairs, nodes at p = 2)
 // the lanes share more lines and reading them alone is faster (p = 2, 110 k particles:
-// 3.7 ms alone, 4.3 together).
+// 3.7 ms alone, 4.3 together), as it is with the potential, which takes more registers.
 __device__ __forceinline__ void ew_fetch(const float *__restrict__ tab, uint32_t point, ew_f4 *buf,
                                          float (&r)[G4_EWALD_NCOMP])
 {

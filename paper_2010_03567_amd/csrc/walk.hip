@@ -383,7 +383,9 @@ __device__ __forceinline__ void eval_p2m(const WalkArgs &A, WaveLds<POT> &W, uin
                                          ew_f4 *ewbuf)
 {
     // kernel 3 at p = 3: all lanes fetch the table together, the idle ones repeat the first pair
-    constexpr bool FETCH = KER == 3 && ORD3;
+    // (not with the potential, where the row's registers cost more than the lines saved: 20 k
+    // particles 1.93 ms alone, 2.05 together, 110 k 3.03 and 3.13)
+    constexpr bool FETCH = KER == 3 && ORD3 && !POT;
     const bool on = (uint32_t)lane < n;
     if (!FETCH && !on) return;
     const uint32_t q = (head + (FETCH && !on ? 0 : lane)) & (WK_RING - 1);
@@ -442,8 +444,8 @@ __device__ __forceinline__ void eval_p2m(const WalkArgs &A, WaveLds<POT> &W, uin
         // the other images: g = 1/r - psi, so the node adds +f (force) and +phi_psi (potential)
         float cx, cy, cz, cp = 0.f;
         EwPoint p = ew_locate(A.ew, A.ew_n, A.ew_h, A.ew_hinv, dx, dy, dz);
-        float row[ORD3 ? G4_EWALD_NCOMP : 1];
-        if constexpr (ORD3) {
+        float row[FETCH ? G4_EWALD_NCOMP : 1];
+        if constexpr (FETCH) {
             // the quadrupole force takes psi's derivatives to order 6, the whole row
             ew_fetch(A.ew, p.point, ewbuf, row);
             p.row = row;
@@ -477,7 +479,7 @@ __global__ __launch_bounds__(256, WALK_MIN_WAVES(KER, POT, HI)) void k_walk(cons
     __shared__ WaveLds<POT> lds[4];
     const int lane = threadIdx.x & 63;
     WaveLds<POT> &W = lds[threadIdx.x >> 6];
-    constexpr bool FETCH = KER == 3 && ORD3;
+    constexpr bool FETCH = KER == 3 && ORD3 && !POT;
     __shared__ ew_f4 ewlds[FETCH ? 4 : 1][FETCH ? 256 : 1];  // table rows under way (ew_fetch)
     ew_f4 *const ewb = ewlds[FETCH ? threadIdx.x >> 6 : 0];
     uint4 *const spill = A.spill + (size_t)(blockIdx.x * 4 + (threadIdx.x >> 6)) * WK_SPILL;
