@@ -756,13 +756,16 @@ __global__ __launch_bounds__(512) void k_moments_block(const DevCounters *__rest
 }
 
 // Levels 0 to MOM_TOP hold at most 73 nodes (per box): one block takes them, a launch
-// instead of one per level.  So do the levels from MOM_DEEP on of a set of at most
+// instead of one per level, unless they may hold large leaves, which one compute unit reads
+// more slowly (2 10^6 particles, leaf 10^5 or two levels: 11.8 ms by level, 13.2 by the block;
+// leaf 1000 0.88 and 0.89).  So do the levels from MOM_DEEP on of a set of at most
 // MOM_DEEP_N particles.  A larger set may have thousands of nodes that deep, where it is
 // the dense core of a larger one, and 64 groups of lanes are too few for them: 16384
 // particles in 10^-4 of the box side, leaf 4, 155 us with a launch per level and 707 with
 // the block (leaf 16: 144, 353); 1024 in 10^-4, leaf 1, 181, 200; 500 184, 168; ordinary
 // sets of 1000 87, 78, of 8192 (leaf 16) 97, 91.
 #define MOM_TOP 2
+#define MOM_TOP_LEAF 1024
 #define MOM_DEEP 17
 #define MOM_DEEP_N 512
 
@@ -774,7 +777,7 @@ int g4_launch_moments(g4_ctx *ctx, g4_tree *t)
         k_moments_block<float><<<1, 512, 0, s>>>(t->ctr, t->parts, t->wn, t->mom, t->q3, t->leafof, l, MOM_DEEP, t->unit);
         l = MOM_DEEP - 1;
     }
-    const int top = t->nbox <= 8 ? MOM_TOP : -1;
+    const int top = t->nbox <= 8 && l > MOM_TOP && t->tp.leaf_max <= MOM_TOP_LEAF ? MOM_TOP : -1;
     for (; l > top; l--) {
         if (l <= G4_FP64_LEVELS)
             k_moments<double><<<grid_for(t->n, 1024), kBlock, 0, s>>>(t->ctr, t->parts, t->wn, t->mom, t->q3, t->leafof, l,
