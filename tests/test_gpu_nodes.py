@@ -95,3 +95,21 @@ def test_forest_nodes(g, B):
         assert np.array_equal(ex["first"][sel] - lo, one["first"])
         for k in ("level", "cell", "count", "leaf", "com", "q2", "q3"):
             assert np.array_equal(ex[k][sel], one[k]), k
+
+
+# windows in memory, eight values a pass: leaf sizes at powers of eight, sets of one more than a leaf, odd ends
+@pytest.mark.parametrize("n,B", [(1026, 1025), (4111, 1026), (4098, 4097), (20011, 4094), (20011, 4095), (20011, 4096),
+                                 (70003, 32767), (70003, 32768), (70002, 70001), (70002, 70002), (70001, 100000)])
+def test_nodes_of_large_leaves(g, n, B):
+    ctx = g.Context()
+    pos = points(n, n + B)
+    tp = g.tree_params(True, 1.0, leaf_max=B)
+    x, y, z = g.g4_quantize(ctx, torch.from_numpy(pos).cuda(), tp)
+    tree = g.g4_build_tree(ctx, g.particles(x, y, z, torch.ones(n, device="cuda")), tp)
+    ex = export(g, ctx, tree)
+    X, Y, Z = (v.cpu().numpy().view(np.uint32) for v in (x, y, z))
+    level, cell, count, leaf = oracle.Tree(X, Y, Z, np.ones(n), True, 1.0, B).nodes()
+    mine = np.column_stack([ex["level"], ex["cell"].view(np.uint32), ex["count"], ex["leaf"]]).astype(np.int64)
+    ref = np.column_stack([level, cell, count, leaf]).astype(np.int64)
+    assert np.array_equal(mine[np.lexsort(mine.T)], ref[np.lexsort(ref.T)])
+    check_links(ex, n)
