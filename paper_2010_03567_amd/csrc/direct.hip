@@ -391,9 +391,11 @@ static void launch_direct_tb(DirectArgs A, hipStream_t s)
     // pairs, which differ much from block to block, more evenly spread (reach 0.075: 300
     // targets of 10^6 0.66 ms at 16 wavefronts, 0.68 at 8, 0.97 at 4; 10^4 targets 4.92, 4.28, 4.91)
     const int64_t blocks = (A.nt + TB - 1) / TB;
-    if (blocks < 1024) {
-        k_direct<KER, TB, 16, FAR><<<(unsigned)blocks, 1024, 0, s>>>(A);
-        return;
+    if constexpr (TB < 8) {  // 8 targets a block only from 8192 on
+        if (blocks < 1024) {
+            k_direct<KER, TB, 16, FAR><<<(unsigned)blocks, 1024, 0, s>>>(A);
+            return;
+        }
     }
     for (int64_t b = 0; b < blocks; b += DIRECT_BLOCKS) {
         A.t0 = b * TB;
