@@ -239,9 +239,9 @@ int g4_quantize(g4_ctx *ctx, const double *pos, int64_t n, const g4_tree_params 
  * worst case N + max_depth * N/(B+1) nodes, key sort buffers, moments). */
 int g4_workspace_bytes(const g4_tree_params *tp, int64_t n, size_t *bytes);
 
-/* Build the octree over Morton-sorted particles (Sec. "Geometry of the
- * tree"): quantised coordinates -> 63-bit Morton keys -> stable radix sort ->
- * level-synchronous node splitting.  ws: device buffer of ws_bytes (kept by
+/* Build the octree over curve-sorted particles (Sec. "Geometry of the
+ * tree"): quantised coordinates -> 63-bit curve keys -> stable radix sort ->
+ * the nodes of all levels from the sorted keys.  ws: device buffer of ws_bytes (kept by
  * the tree until g4_tree_free; the particle arrays are copied into it).
  * *out receives a host handle. */
 int g4_build_tree(g4_ctx *ctx, const g4_particles *p, const g4_tree_params *tp, void *ws, size_t ws_bytes,
@@ -452,8 +452,9 @@ int g4_fmm_force(g4_ctx *ctx, g4_tree *tree, const g4_fmm_params *fp, double lis
 /* g4_fmm_force without a workspace argument, for callers that cannot
  * allocate device memory (code under HIP graph capture, tight serving loops,
  * harnesses that forbid allocation).  The FMM's lists, field expansions and
- * accumulators live in a static 64 MiB device array that the library holds
- * on every device it runs on until the process ends; the call itself
+ * accumulators live in a static device array (64 MiB beside the call's
+ * counters) that the library holds on every device it runs on until the
+ * process ends; the call itself
  * allocates nothing.  It uses the largest list factor (4, 2 or 1) whose
  * workspace fits and returns G4_EINVAL with the sizes in the message when
  * even factor 1 does not (about 500 bytes per particle at leaf 16: trees up

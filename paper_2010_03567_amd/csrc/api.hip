@@ -249,8 +249,7 @@ int g4_tree_info(g4_ctx *ctx, const g4_tree *tree, int64_t *nnodes, int64_t *lev
     G4_HIP(ctx, hipStreamSynchronize(ctx->stream));
     if (nnodes) *nnodes = h.node_count;
     if (level_start) {
-        // levels are stored one after another, so the starts are the running
-        // sums of the level sizes (the device keeps starts only for non-empty levels)
+        // levels are stored one after another, so the starts are the running sums of the level sizes
         const int maxd = tree->tp.max_depth;
         level_start[0] = 0;
         for (int l = 0; l <= maxd; l++) level_start[l + 1] = level_start[l] + h.lvl_count[l];

@@ -1,5 +1,5 @@
-// build.hip -- integer mapping, Morton keys, radix sort, level-synchronous
-// octree construction and the upward multipole pass on gfx950.
+// build.hip -- integer mapping, curve keys, the octree's nodes from the sorted
+// keys (all levels at once) and the upward multipole pass on gfx950.
 //
 // Paper: Sec. "Integer coordinates" (fixed-point positions, two's-complement
 // nearest image), Sec. "Non-periodic potentials" (isolated root mapped into a
@@ -966,9 +966,9 @@ int g4_launch_gather_seed(g4_ctx *ctx, g4_tree *t, const float *a_seed_caller)
 }
 
 // ------------------------------------------------------------------ forest
-// Many independent boxes in one node array: particles sorted by (box, Morton
-// key), one root per box at level 0 (nodes 0..nbox-1), then the same
-// level-synchronous split and upward pass as a single tree.
+// Many independent boxes in one node array: particles sorted by (box, curve
+// key), one root per box at level 0 (nodes 0..nbox-1); nodes and moments as for
+// a single tree, with a new root wherever the box changes.
 
 // box of each Morton-sorted particle (caller index -> box by binary search)
 __global__ void k_boxkey(const uint32_t *__restrict__ perm, int64_t n, const int64_t *__restrict__ off, int nbox,

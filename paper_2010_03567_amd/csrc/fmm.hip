@@ -76,7 +76,7 @@ struct FmmArgs {
     // frontier and entry lists
     const uint2 *fin;
     uint2 *fout;
-    uint32_t *cnt;   // [2] node entries, [3] particle entries, [4] overflow (FMM_* below)
+    uint32_t *cnt;   // counter words of the call, at the FMM_* places above
     uint32_t *cin, *cout, *cnext;  // this pass's and the next one's frontier sizes; the one after, cleared
     uint32_t cap_pairs;
     // entries: key = target << kshift | order key of the source, value = source (type bits | index)
@@ -958,7 +958,7 @@ struct FastArgs {
     float ew_h, ew_hinv;
     const uint2 *fin;
     uint2 *fout;
-    uint32_t *cnt;  // [2] leaf pairs, [3] leaf-node pairs, [4] overflow (FMM_* below)
+    uint32_t *cnt;  // counter words of the call, at the FMM_* places
     uint32_t *cin, *cout, *cnext;  // as in FmmArgs
     uint32_t cap_pairs;
     uint2 *ll;      // opened (leaf, leaf) pairs
